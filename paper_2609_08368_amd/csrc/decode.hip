@@ -489,53 +489,27 @@ __device__ __forceinline__ void for_each_piece(const DecodeArgs& a, int w, F&& f
   }
 }
 
-// A lane's share of one key row of one KV head, as four 8-element chunks of
-// the head dimension: chunk c of lane group grp holds elements d0 = 32 grp +
-// 8 c .. d0 + 7, so a lane's chunks are contiguous (64 bytes of bf16, or 32
-// bytes of FP8 codes: two 16-byte loads rather than four 8-byte ones, which
-// would move half the bytes per load instruction). The scores only need Q and
-// K in the same order, and V is staged into LDS by position. Rows are kept as
-// loaded and converted where they are used.
-template <bool kFp8>
-struct RowPart;
-template <>
-struct RowPart<false> {
-  bf16x8 r[4];
-  __device__ static int d0(int c, int grp) { return 32 * grp + 8 * c; }
-  __device__ void load(const char* row, int grp) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) r[c] = *reinterpret_cast<const bf16x8*>(row + 2 * d0(c, grp));
-  }
-  __device__ bf16x8 chunk(int c) const { return r[c]; }
-};
-template <>
-struct RowPart<true> {
-  uint4 r[2];
-  __device__ static int d0(int c, int grp) { return 32 * grp + 8 * c; }
-  __device__ void load(const char* row, int grp) {
-    r[0] = *reinterpret_cast<const uint4*>(row + 32 * grp);
-    r[1] = *reinterpret_cast<const uint4*>(row + 32 * grp + 16);
-  }
-  __device__ bf16x8 chunk(int c) const {
-    const uint4 w = r[c >> 1];
-    return kv_to_bf16x8<true>((c & 1) ? make_uint2(w.z, w.w) : make_uint2(w.x, w.y));
-  }
-};
+// First element of 8-element chunk c of lane group grp's share of a head row:
+// a lane's four chunks are contiguous (the scores only need Q and K in the same
+// order, and V is staged into LDS by position).
+__device__ __forceinline__ int head_elem(int c, int grp) { return 32 * grp + 8 * c; }
 
 // Split-KV decode on MFMA for a packed GQA group of up to 16 query heads.
 // One wave per (private item, KV head, 16-head block). Keys are processed 32
-// at a time. With pages of at least 32 keys, K and V rows are loaded whole
-// (every instruction reads whole rows) with non-temporal loads and staged in
-// the wave's own LDS tiles; K is read back as the A operand of S^T = K Q^T
-// and V transposed as the A operand of O^T += V^T P^T. Measured on the ragged
-// 64K batch: 1.50-1.56 ms per kernel (6.7-6.9 TB/s) against 1.68-1.69 ms with
-// K loaded straight into A-operand registers (each lane its RowPart of a row,
-// so an instruction reads 64-byte pieces of 16 rows, which non-temporal
-// loads fetch again per piece) and V staged the same way; FP8 pages 0.84
-// against 0.89 ms (with 8-byte loads, 16 lanes per row, 0.93 ms). Pages of
-// fewer than 32 keys keep the RowPart path. Rows are fetched one tile ahead
+// at a time: K and V rows are loaded whole (every instruction reads whole
+// rows) with non-temporal loads and staged in the wave's own LDS tiles; K is
+// read back as the A operand of S^T = K Q^T and V transposed as the A operand
+// of O^T += V^T P^T. HBM-bound. Measured on the ragged 64K batch: 1.50-1.56 ms
+// per kernel (6.7-6.9 TB/s) against 1.68-1.69 ms with K loaded straight into
+// A-operand registers (each lane 64 contiguous bytes of a row, so an
+// instruction reads pieces of 16 rows, which non-temporal loads fetch again per
+// piece) and V staged the same way; FP8 pages 0.84 against 0.89 ms (with 8-byte
+// loads, 16 lanes per row, 0.93 ms). kIds page ids cover a tile: one
+// where a page holds 32 keys, two for 16-key and four for 8-key pages (12
+// sequences of 0.3-6K keys, 16-key pages, 32/8 heads, whole call: 52.8 us with
+// K in A-operand registers, 46.2 us this way). Rows are fetched one tile ahead
 // (bf16) or two (FP8), and page ids one tile ahead of the rows they address.
-template <bool kFp8>
+template <bool kFp8, int kIds>
 __global__ __launch_bounds__(512) void decode_mfma_kernel(DecodeArgs a) {
   // dynamic LDS: per wave a V tile and a K tile (32 keys x 272 B each)
   extern __shared__ u16 vs_dyn[];
@@ -571,7 +545,7 @@ __global__ __launch_bounds__(512) void decode_mfma_kernel(DecodeArgs a) {
   {
     const __bf16* qp = (const __bf16*)a.q + (int64_t)b * a.q_sb + (int64_t)h * a.q_sh;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) qv[c] = col_ok ? load_bf16x8(qp + RowPart<kFp8>::d0(c, grp)) : zero_bf16x8();
+    for (int c = 0; c < 4; ++c) qv[c] = col_ok ? load_bf16x8(qp + head_elem(c, grp)) : zero_bf16x8();
   }
 
   f32x4 o[8];
@@ -587,195 +561,156 @@ __global__ __launch_bounds__(512) void decode_mfma_kernel(DecodeArgs a) {
   const uint32_t ksp = (uint32_t)a.kv.sp, kss = (uint32_t)a.kv.ss;
   const uint32_t vsp = (uint32_t)a.kv.v_sp, vss = (uint32_t)a.kv.v_ss;
   const int pmask = a.kv.page_size - 1;
-  // tiles start at multiples of 32 keys, so a page of >= 32 keys holds a whole tile
-  const bool page_holds_tile = a.kv.page_size >= kTile && (t_begin & (kTile - 1)) == 0;
-
-  // The two ways of finding a tile's pages are separate code paths, so the
-  // scalar page ids of the first never merge with the vector ones of the other.
-  auto run = [&](auto holds_tag) {
-    constexpr bool kHolds = decltype(holds_tag)::value;
-    // Rows of the next kDepth tiles are in flight while a tile is computed.
-    // FP8 rows are half the bytes, so they go two tiles ahead (the same bytes
-    // and registers in flight as one bf16 tile).
-    constexpr int kDepth = kFp8 ? 2 : 1;
-    // Rows in flight. kWhole (one page per tile): whole rows, loaded
-    // non-temporally 16 bytes per lane and staged in LDS; bf16: 16 lanes per
-    // 256-byte row (lane l: elements 8 (l % 16) .. + 7 of rows 4 i + l / 16),
-    // FP8: 8 lanes per 128-byte row (lane l: codes 16 (l % 8) .. + 15 of rows
-    // 8 i + l / 8). Otherwise each lane's RowPart of keys 16 hh + col, K kept
-    // in registers.
-    constexpr bool kWhole = kHolds;
-    typedef std::conditional_t<kFp8, uint4, bf16x8> Piece;
-    struct WholeRows {
-      Piece r[kFp8 ? 4 : 8];
-    };
-    typedef std::conditional_t<kWhole, WholeRows, RowPart<kFp8>[2]> Rows;
-    Rows kc0, kc1, vc0, vc1;
-    int praw[2];                        // page ids of the next tile to fetch
-    // When a page holds the whole tile its id is the same for the wave and is
-    // read through the scalar unit (the block table is not written while the
-    // kernel runs). Its wait then does not include the vector loads of rows
-    // issued before it, which retire in order.
-    typedef __attribute__((address_space(4))) const int ConstInt;
-    const ConstInt* bt_c = (const ConstInt*)bt_row;
-    auto fetch_pages = [&](int t0) {
-      if constexpr (kHolds) {
-        const int t = __builtin_amdgcn_readfirstlane(t0 < t_end ? t0 : t_end - 1);
-        praw[0] = bt_c[__umul24((uint32_t)(t >> a.kv.log2_page), bt_sj)];
-        praw[1] = 0;
-      } else {
+  // Rows of the next kDepth tiles are in flight while a tile is computed.
+  // FP8 rows are half the bytes, so they go two tiles ahead (the same bytes
+  // and registers in flight as one bf16 tile).
+  constexpr int kDepth = kFp8 ? 2 : 1;
+  // Rows in flight: whole rows, loaded non-temporally 16 bytes per lane and
+  // staged in LDS; bf16: 16 lanes per 256-byte row (lane l: elements 8 (l % 16)
+  // .. + 7 of rows 4 i + l / 16), FP8: 8 lanes per 128-byte row (lane l: codes
+  // 16 (l % 8) .. + 15 of rows 8 i + l / 8).
+  typedef std::conditional_t<kFp8, uint4, bf16x8> Piece;
+  constexpr int kN = kFp8 ? 4 : 8;
+  struct Rows {
+    Piece r[kN];
+  };
+  Rows kc0, kc1, vc0, vc1;
+  // Page ids of the next tile to fetch, one per 32 / kIds keys (a piece starts
+  // on a page boundary or a multiple of 32 keys past one, so each such run of
+  // keys lies in one page). They are the same for the wave and are read
+  // through the scalar unit (the block table is not written while the kernel
+  // runs): their wait then does not include the vector loads of rows issued
+  // before them, which retire in order.
+  int praw[kIds];
+  typedef __attribute__((address_space(4))) const int ConstInt;
+  const ConstInt* bt_c = (const ConstInt*)bt_row;
+  auto fetch_pages = [&](int t0) {
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          int t = t0 + 16 * hh + col;
-          t = t < t_end ? t : t_end - 1;
-          praw[hh] = bt_row[__umul24((uint32_t)(t >> a.kv.log2_page), bt_sj)];
-        }
+    for (int u = 0; u < kIds; ++u) {
+      const int tu = t0 + u * (kTile / kIds);
+      const int t = __builtin_amdgcn_readfirstlane(tu < t_end ? tu : t_end - 1);
+      praw[u] = bt_c[__umul24((uint32_t)(t >> a.kv.log2_page), bt_sj)];
+    }
+  };
+  auto fetch_rows = [&](int t0, Rows& kc, Rows& vc) {
+    int pg[kIds];
+#pragma unroll
+    for (int u = 0; u < kIds; ++u) {
+      pg[u] = praw[u];
+      if ((unsigned)pg[u] >= (unsigned)a.kv.num_pages) {
+        bad = 1;
+        pg[u] = pg[u] < 0 ? 0 : a.kv.num_pages - 1;
       }
-    };
-    auto fetch_rows = [&](int t0, Rows& kc, Rows& vc) {
-      if constexpr (kWhole) {
-        int pg = praw[0];
-        if ((unsigned)pg >= (unsigned)a.kv.num_pages) {
-          bad = 1;
-          pg = pg < 0 ? 0 : a.kv.num_pages - 1;
-        }
-        constexpr int kRowsPer = kFp8 ? 8 : 4, kLanesPerRow = 64 / kRowsPer, kN = kFp8 ? 4 : 8;
-        const int piece = (kFp8 ? 16 : 8) * (lane & (kLanesPerRow - 1));
+    }
+    constexpr int kRowsPer = kFp8 ? 8 : 4, kLanesPerRow = 64 / kRowsPer;
+    const int piece = (kFp8 ? 16 : 8) * (lane & (kLanesPerRow - 1));
 #pragma unroll
-        for (int i = 0; i < kN; ++i) {
-          int t = t0 + kRowsPer * i + lane / kLanesPerRow;
-          t = t < t_end ? t : t_end - 1;
-          kc.r[i] = load_nt<Piece>(kbase + ES * (row_offset((uint32_t)pg, ksp, t & pmask, kss) + piece));
-          vc.r[i] = load_nt<Piece>(vbase + ES * (row_offset((uint32_t)pg, vsp, t & pmask, vss) + piece));
-        }
-      } else {
+    for (int i = 0; i < kN; ++i) {
+      int t = t0 + kRowsPer * i + lane / kLanesPerRow;
+      t = t < t_end ? t : t_end - 1;
+      const uint32_t p = (uint32_t)pg[i * kIds / kN];
+      kc.r[i] = load_nt<Piece>(kbase + ES * (row_offset(p, ksp, t & pmask, kss) + piece));
+      vc.r[i] = load_nt<Piece>(vbase + ES * (row_offset(p, vsp, t & pmask, vss) + piece));
+    }
+  };
+  // one tile of keys [t0, t0 + 32) from the rows in (kc, vc), which then take
+  // the rows kDepth tiles ahead. Prefetches past the piece are clamped to its
+  // last key (in bounds, and never used): unconditional loads keep the number
+  // of loads in flight the same on every path, so each wait covers only the
+  // tile it needs.
+  auto tile = [&](int t0, Rows& kc, Rows& vc) {
+    __syncthreads();  // previous tile's K and V reads are done
+    const int tn = t0 + kDepth * kTile;
+    // stage both tiles, then the rows kDepth tiles ahead take the
+    // registers at once
+    if constexpr (kFp8) {
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          int t = t0 + 16 * hh + col;
-          t = t < t_end ? t : t_end - 1;
-          int pg = praw[kHolds ? 0 : hh];
-          if ((unsigned)pg >= (unsigned)a.kv.num_pages) {
-            bad = 1;
-            pg = pg < 0 ? 0 : a.kv.num_pages - 1;
-          }
-          kc[hh].load(kbase + ES * row_offset((uint32_t)pg, ksp, t & pmask, kss), grp);
-          vc[hh].load(vbase + ES * row_offset((uint32_t)pg, vsp, t & pmask, vss), grp);
-        }
+      for (int i = 0; i < 4; ++i) {
+        const int row = 8 * i + (lane >> 3), e0 = 16 * (lane & 7);
+        const uint4 kw = kc.r[i], vw = vc.r[i];
+        *reinterpret_cast<bf16x8*>(&vs[row][e0]) = kv_to_bf16x8<true>(make_uint2(vw.x, vw.y));
+        *reinterpret_cast<bf16x8*>(&vs[row][e0 + 8]) = kv_to_bf16x8<true>(make_uint2(vw.z, vw.w));
+        *reinterpret_cast<bf16x8*>(&ks[row][e0]) = kv_to_bf16x8<true>(make_uint2(kw.x, kw.y));
+        *reinterpret_cast<bf16x8*>(&ks[row][e0 + 8]) = kv_to_bf16x8<true>(make_uint2(kw.z, kw.w));
       }
-    };
-    // one tile of keys [t0, t0 + 32) from the rows in (kc, vc), which then take
-    // the rows kDepth tiles ahead. Prefetches past the piece are clamped to its
-    // last key (in bounds, and never used): unconditional loads keep the number
-    // of loads in flight the same on every path, so each wait covers only the
-    // tile it needs.
-    auto tile = [&](int t0, Rows& kc, Rows& vc) {
-      __syncthreads();  // previous tile's K and V reads are done
-      const int tn = t0 + kDepth * kTile;
-      if constexpr (kWhole) {
-        // stage both tiles, then the rows kDepth tiles ahead take the
-        // registers at once
-        if constexpr (kFp8) {
+    } else {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int row = 8 * i + (lane >> 3), e0 = 16 * (lane & 7);
-            const uint4 kw = kc.r[i], vw = vc.r[i];
-            *reinterpret_cast<bf16x8*>(&vs[row][e0]) = kv_to_bf16x8<true>(make_uint2(vw.x, vw.y));
-            *reinterpret_cast<bf16x8*>(&vs[row][e0 + 8]) = kv_to_bf16x8<true>(make_uint2(vw.z, vw.w));
-            *reinterpret_cast<bf16x8*>(&ks[row][e0]) = kv_to_bf16x8<true>(make_uint2(kw.x, kw.y));
-            *reinterpret_cast<bf16x8*>(&ks[row][e0 + 8]) = kv_to_bf16x8<true>(make_uint2(kw.z, kw.w));
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            *reinterpret_cast<bf16x8*>(&vs[4 * i + (lane >> 4)][8 * (lane & 15)]) = kv_to_bf16x8<kFp8>(vc.r[i]);
-            *reinterpret_cast<bf16x8*>(&ks[4 * i + (lane >> 4)][8 * (lane & 15)]) = kv_to_bf16x8<kFp8>(kc.r[i]);
-          }
-        }
-        fetch_rows(tn, kc, vc);
-        fetch_pages(tn + kTile);
-        // the wave reads the K rows its other lanes wrote
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      } else {
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            *reinterpret_cast<bf16x8*>(&vs[16 * hh + col][RowPart<kFp8>::d0(c, grp)]) = vc[hh].chunk(c);
+      for (int i = 0; i < 8; ++i) {
+        *reinterpret_cast<bf16x8*>(&vs[4 * i + (lane >> 4)][8 * (lane & 15)]) = kv_to_bf16x8<kFp8>(vc.r[i]);
+        *reinterpret_cast<bf16x8*>(&ks[4 * i + (lane >> 4)][8 * (lane & 15)]) = kv_to_bf16x8<kFp8>(kc.r[i]);
       }
-      f32x4 st[2];
+    }
+    fetch_rows(tn, kc, vc);
+    fetch_pages(tn + kTile);
+    // the wave reads the K rows its other lanes wrote
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    f32x4 st[2];
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh) st[hh] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int hh = 0; hh < 2; ++hh) st[hh] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          bf16x8 ka;
-          if constexpr (kWhole)
-            ka = *reinterpret_cast<const bf16x8*>(&ks[16 * hh + col][RowPart<kFp8>::d0(c, grp)]);
-          else
-            ka = kc[hh].chunk(c);
-          st[hh] = mfma_16x16x32(ka, qv[c], st[hh]);
-        }
-      if constexpr (!kWhole) {
-        fetch_rows(tn, kc, vc);
-        fetch_pages(tn + kTile);
+      for (int hh = 0; hh < 2; ++hh) {
+        const bf16x8 ka = *reinterpret_cast<const bf16x8*>(&ks[16 * hh + col][head_elem(c, grp)]);
+        st[hh] = mfma_16x16x32(ka, qv[c], st[hh]);
       }
 
-      float mt = kNegInf;
+    float mt = kNegInf;
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh)
+    for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int t = t0 + 16 * hh + 4 * grp + i;
-          if (t >= t_end) st[hh][i] = kNegInf;
-          mt = fmaxf(mt, st[hh][i]);
-        }
-      mt = group_max(mt) * sl2;
-      const float m_new = fmaxf(m_run, mt);
-      const float alpha = exp2_fast(m_run - m_new);
-      const float neg_m = -m_new;
-      float ps = 0.f;
-      bf16x8 pb;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float p = exp2_fast(fmaf(st[e >> 2][e & 3], sl2, neg_m));
-        ps += p;
-        pb[e] = (__bf16)p;
+      for (int i = 0; i < 4; ++i) {
+        const int t = t0 + 16 * hh + 4 * grp + i;
+        if (t >= t_end) st[hh][i] = kNegInf;
+        mt = fmaxf(mt, st[hh][i]);
       }
-      l_run = l_run * alpha + ps;
-      m_run = m_new;
+    mt = group_max(mt) * sl2;
+    const float m_new = fmaxf(m_run, mt);
+    const float alpha = exp2_fast(m_run - m_new);
+    const float neg_m = -m_new;
+    float ps = 0.f;
+    bf16x8 pb;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) o[j] *= alpha;
-      __syncthreads();  // V tile visible
-      // V^T operand: element e of lane (grp, col) is V[tok(e)][16 j + col], tok(e) =
-      // 4 grp + e (e < 4) or 16 + 4 grp + e - 4 (the keys of pb). With FP8 pages
-      // two transposed reads per MFMA give it: lane 4e + q of a 16-lane block
-      // addresses row 4 grp + e (then 16 rows further), columns 16 j + 4 q ..
-      // + 3, and the read hands lane i element i % 4 of lane 4e + i / 4's chunk
-      // as its element e (FP8 decode 0.834 -> 0.816 ms on the ragged batch).
-      // bf16 keeps eight 16-bit reads: the transposed form measured 0.5-0.9%
-      // slower there, its registers allocated differently.
-      const int tr_row = 4 * grp + ((lane & 15) >> 2), tr_col = 4 * (lane & 3);
+    for (int e = 0; e < 8; ++e) {
+      const float p = exp2_fast(fmaf(st[e >> 2][e & 3], sl2, neg_m));
+      ps += p;
+      pb[e] = (__bf16)p;
+    }
+    l_run = l_run * alpha + ps;
+    m_run = m_new;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        bf16x8 va;
-        if constexpr (kFp8) {
-          const u16* vp = &vs[tr_row][16 * j + tr_col];
-          const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)vp);
-          const i16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vp + 16 * (kHeadDim + 8)));
-          va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7));
-        } else {
+    for (int j = 0; j < 8; ++j) o[j] *= alpha;
+    __syncthreads();  // V tile visible
+    // V^T operand: element e of lane (grp, col) is V[tok(e)][16 j + col], tok(e) =
+    // 4 grp + e (e < 4) or 16 + 4 grp + e - 4 (the keys of pb). With FP8 pages
+    // two transposed reads per MFMA give it: lane 4e + q of a 16-lane block
+    // addresses row 4 grp + e (then 16 rows further), columns 16 j + 4 q ..
+    // + 3, and the read hands lane i element i % 4 of lane 4e + i / 4's chunk
+    // as its element e (FP8 decode 0.834 -> 0.816 ms on the ragged batch).
+    // bf16 keeps eight 16-bit reads: the transposed form measured 0.5-0.9%
+    // slower there, its registers allocated differently.
+    const int tr_row = 4 * grp + ((lane & 15) >> 2), tr_col = 4 * (lane & 3);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int tok = e < 4 ? 4 * grp + e : 16 + 4 * grp + (e - 4);
-            va[e] = bits_to_bf16(vs[tok][16 * j + col]);
-          }
+    for (int j = 0; j < 8; ++j) {
+      bf16x8 va;
+      if constexpr (kFp8) {
+        const u16* vp = &vs[tr_row][16 * j + tr_col];
+        const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)vp);
+        const i16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vp + 16 * (kHeadDim + 8)));
+        va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7));
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int tok = e < 4 ? 4 * grp + e : 16 + 4 * grp + (e - 4);
+          va[e] = bits_to_bf16(vs[tok][16 * j + col]);
         }
-        o[j] = mfma_16x16x32(va, pb, o[j]);
       }
-    };
+      o[j] = mfma_16x16x32(va, pb, o[j]);
+    }
+  };
+  if (t_begin < t_end) {
     fetch_pages(t_begin);
     fetch_rows(t_begin, kc0, vc0);
     if constexpr (kDepth == 2) {
@@ -794,12 +729,6 @@ __global__ __launch_bounds__(512) void decode_mfma_kernel(DecodeArgs a) {
         tile(t0 + kTile, kc1, vc1);
       }
     }
-  };
-  if (t_begin < t_end) {
-    if (page_holds_tile)
-      run(std::true_type{});
-    else
-      run(std::false_type{});
   }
 
   const HeadResult res = finish(m_run, group_sum(l_run));
@@ -1205,6 +1134,18 @@ __global__ __launch_bounds__(64) void merge_kernel(MergeArgs a) {
   if (a.lse_out && lane == 0) a.lse_out[(int64_t)n * a.lo_sn + (int64_t)h * a.lo_sh] = lse_v;
 }
 
+// Page ids per 32-key tile of decode_mfma_kernel (pages hold at least 8 keys);
+// its own kernel each, so the common case keeps its register allocation.
+template <typename F>
+void with_tile_ids(int page_size, F&& f) {
+  if (page_size >= kTile)
+    f(std::integral_constant<int, 1>{});
+  else if (page_size >= kTile / 2)
+    f(std::integral_constant<int, 2>{});
+  else
+    f(std::integral_constant<int, 4>{});
+}
+
 template <bool kFp8>
 void launch_decode_kernels(const DecodeArgs& a, hipStream_t stream, KernelTimer* timer) {
   const unsigned per_item = a.R == 1 ? a.Hkv : a.Hkv * ((a.R + 15) / 16);
@@ -1220,13 +1161,15 @@ void launch_decode_kernels(const DecodeArgs& a, hipStream_t stream, KernelTimer*
     const unsigned nch = per_item / a.item_waves;
     const unsigned grid = (unsigned)((int64_t)a.max_workers * nch);
     const size_t lds = (size_t)2 * a.item_waves * kTile * (kHeadDim + 8) * sizeof(u16);
-    decode_mfma_kernel<kFp8><<<grid, 64 * a.item_waves, lds, stream>>>(a);
+    with_tile_ids(a.kv.page_size, [&](auto ids) {
+      decode_mfma_kernel<kFp8, decltype(ids)::value><<<grid, 64 * a.item_waves, lds, stream>>>(a);
+    });
   }
   if (timer) (void)hipEventRecord(timer->stop, stream);
 }
 
 template <bool kFp8>
-int workers_per_cu_of(int R, int Hkv, int item_waves, int n_tok) {
+int workers_per_cu_of(int R, int Hkv, int item_waves, int n_tok, int page_size) {
   int blocks = 0;
   // multi-token decode: one worker per CU; a worker's Hkv x row-block
   // workgroups then run in equal rounds
@@ -1236,8 +1179,11 @@ int workers_per_cu_of(int R, int Hkv, int item_waves, int n_tok) {
     return blocks / Hkv > 1 ? blocks / Hkv : 1;
   }
   const size_t lds = (size_t)2 * item_waves * kTile * (kHeadDim + 8) * sizeof(u16);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, decode_mfma_kernel<kFp8>, 64 * item_waves, lds) != hipSuccess)
-    blocks = 0;
+  with_tile_ids(page_size, [&](auto ids) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, decode_mfma_kernel<kFp8, decltype(ids)::value>,
+                                                     64 * item_waves, lds) != hipSuccess)
+      blocks = 0;
+  });
   const int nch = Hkv * ((R + 15) / 16) / item_waves;
   return blocks / nch > 1 ? blocks / nch : 1;
 }
@@ -1255,8 +1201,9 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream, KernelTimer* t
   return hipGetLastError();
 }
 
-int decode_workers_per_cu(int R, int Hkv, int item_waves, bool fp8, int n_tok) {
-  return fp8 ? workers_per_cu_of<true>(R, Hkv, item_waves, n_tok) : workers_per_cu_of<false>(R, Hkv, item_waves, n_tok);
+int decode_workers_per_cu(int R, int Hkv, int item_waves, bool fp8, int n_tok, int page_size) {
+  return fp8 ? workers_per_cu_of<true>(R, Hkv, item_waves, n_tok, page_size)
+             : workers_per_cu_of<false>(R, Hkv, item_waves, n_tok, page_size);
 }
 
 hipError_t launch_merge(const MergeArgs& a, hipStream_t stream) {

@@ -212,7 +212,7 @@ double diag_mfma_flops(int iters, int cus);
 
 // Workers of the private decode pass that are resident on one CU at a time
 // (from the kernel's occupancy; a worker is one workgroup per wave group).
-int decode_workers_per_cu(int R, int Hkv, int item_waves, bool fp8, int n_tok);
+int decode_workers_per_cu(int R, int Hkv, int item_waves, bool fp8, int n_tok, int page_size);
 hipError_t launch_extend(const ExtendArgs& a, hipStream_t stream, KernelTimer* timer);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t stream);
 hipError_t launch_append(const AppendArgs& a, hipStream_t stream, KernelTimer* timer);

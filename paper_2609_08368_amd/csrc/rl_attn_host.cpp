@@ -333,17 +333,19 @@ int target_items_for(int64_t Hq, int64_t Hkv, int cus) {
   return (int)std::max<int64_t>(1, (int64_t)cus * env().target_wgs_per_cu / decode_wgs_per_item(Hq, Hkv));
 }
 
-// workers of the private pass resident on one CU (cached per shape)
-int workers_per_cu(int64_t Hq, int64_t Hkv, bool fp8, int n_tok) {
+// workers of the private pass resident on one CU (cached per shape; pages of
+// 8, 16 and at least 32 keys run different kernels)
+int workers_per_cu(int64_t Hq, int64_t Hkv, bool fp8, int n_tok, int64_t P) {
   if (env().workers_per_cu > 0) return env().workers_per_cu;
+  const int page = (int)std::min<int64_t>(P, 32);
   static std::mutex mu;
-  static std::map<std::tuple<int64_t, int64_t, bool, int>, int> cache;
+  static std::map<std::tuple<int64_t, int64_t, bool, int, int>, int> cache;
   std::lock_guard<std::mutex> lk(mu);
-  auto it = cache.find({Hq, Hkv, fp8, n_tok});
+  auto it = cache.find({Hq, Hkv, fp8, n_tok, page});
   if (it != cache.end()) return it->second;
   const int R = (int)(Hq / std::max<int64_t>(1, Hkv));
-  const int n = rl::decode_workers_per_cu(R, (int)Hkv, decode_item_waves(Hq, Hkv), fp8, n_tok);
-  cache[{Hq, Hkv, fp8, n_tok}] = n;
+  const int n = rl::decode_workers_per_cu(R, (int)Hkv, decode_item_waves(Hq, Hkv), fp8, n_tok, page);
+  cache[{Hq, Hkv, fp8, n_tok, page}] = n;
   return n;
 }
 
@@ -396,7 +398,7 @@ DecodeLayout decode_layout_with(int64_t B, int64_t Hq, int64_t Hkv, int64_t max_
 
 DecodeLayout decode_layout(int64_t B, int64_t Hq, int64_t Hkv, int64_t max_pages, int64_t P, int split, int cus,
                            bool prefix_share, bool fp8, int n_tok) {
-  return decode_layout_with(B, Hq, Hkv, max_pages, P, split, cus, workers_per_cu(Hq, Hkv, fp8, n_tok),
+  return decode_layout_with(B, Hq, Hkv, max_pages, P, split, cus, workers_per_cu(Hq, Hkv, fp8, n_tok, P),
                             prefix_share, n_tok);
 }
 

@@ -38,7 +38,7 @@ CASES = [
     (64, 32, 1, [1000, 3], 256),
     (32, 24, 2, [31, 32, 33, 97, 600], 0),   # pages of exactly one 32-key tile: whole-row loads
     (32, 24, 2, [31, 32, 33, 97, 600], 64),
-    (16, 40, 2, [300, 17], 0),               # pages below a tile: each lane loads its share of a row
+    (16, 40, 2, [300, 17], 0),               # pages below a tile: two ids per tile
 ]
 
 
@@ -51,6 +51,27 @@ def test_decode_shapes(case):
     out, lse = H.run_decode(w, t, split_tokens=split)
     ref_o, ref_l = H.oracle_full(w, t)
     H.compare(out, ref_o, lse, ref_l, what=str(case))
+
+
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+@pytest.mark.parametrize("ps,shared", [(8, 40), (8, 8), (16, 48), (32, 32)])
+def test_decode_tiles_after_a_shared_prefix(ps, shared, fp8):
+    """Private tiles that start off a 32-key boundary (behind a prefix of whole pages):
+    every run of 32 / ids keys still lies in one page."""
+    lens = [shared + x for x in (1, 7, 8, 9, 31, 32, 33, 65, 200)]
+    w = wl.custom(31 + ps, "decode", lens, hq=12, hkv=2, page_size=ps, group_size=3, shared_tokens=shared)
+    H.say(f"tiles after a prefix of {shared} keys, P={ps} fp8={fp8}")
+    if fp8:
+        t = wl.materialize_fp8(w, DEV)
+        out, lse = torch.empty_like(t["q"]), torch.empty(t["q"].shape[:2], dtype=torch.float32, device=DEV)
+        ra.decode_fp8(t["q"], t["k_pages"], t["v_pages"], t["k_scale"], t["v_scale"], t["block_table"], t["kv_lens"],
+                      t["scale"], out=out, lse=lse)
+        torch.cuda.synchronize()
+    else:
+        t = wl.materialize(w, DEV)
+        out, lse = H.run_decode(w, t)
+    ref_o, ref_l = H.oracle_full(w, t)
+    H.compare(out, ref_o, lse, ref_l, what=f"P={ps} shared={shared}")
 
 
 def test_decode_single_key_is_exact():
