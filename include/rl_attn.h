@@ -104,8 +104,8 @@ typedef struct {
                             With automatic splits and more than one query token
                             per sequence (q, out and lse with batch stride =
                             tokens x token stride), decode runs as in the
-                            deterministic mode (one extend unit per sequence and
-                            KV head, no split of the keys; faster when no pages
+                            deterministic mode (extend units of a sequence and
+                            KV head; faster when no pages
                             are shared, and batch-invariant): with OFF always;
                             with AUTO and bf16 pages when the device finds no
                             shared prefix page in the batch (both passes are
@@ -114,13 +114,16 @@ typedef struct {
                             kernel reads is range-checked on every call           */
   int32_t deterministic; /* decode: 1 = batch-invariant and equal to extend. Each
                             sequence is computed by the extend kernel as one query
-                            row, with no split of its keys, so its out and lse do
+                            row, its keys merged at fixed key positions (16384,
+                            32768, 65536, ...), so its out and lse do
                             not depend on the other sequences of the batch (their
                             number, order or lengths) and are bitwise equal to
                             rl_attn_extend_ex of that token (paper: section
                             "True-On-Policy Alignment" asks for prefill and decode
                             paths that agree bitwise, and for batch invariance).
-                            Slower on long contexts (no key split). Extend rows
+                            Slower where few long contexts have to fill the
+                            device (the last of these parts is up to half of a
+                            context). Extend rows
                             are always invariant in this sense: a row's result
                             does not depend on the other rows of its chunk, the
                             chunk's length or the batch, so a prefill of a whole
@@ -281,7 +284,10 @@ int rl_attn_reserve_workspace(size_t bytes, void* stream);
  * Decode: query_tokens query tokens per sequence (1 for a 3-D q, n for q
  * [B, n, Hq, 128]) and split_tokens the opts.split_tokens the call will pass
  * (0 = automatic); the size covers bf16 and FP8 pages, prefix sharing on or off
- * and the deterministic mode. Returns 0 for sizes a call would reject. */
+ * and the deterministic mode. Block tables of more than 16384 tokens per sequence
+ * take up to about 300 MB more for extend and deterministic decode (partials
+ * of keys split between workgroups, at most 256 MB, and one state per
+ * workgroup). Returns 0 for sizes a call would reject. */
 size_t rl_attn_decode_workspace_size(int64_t batch, int64_t num_q_heads, int64_t num_kv_heads,
                                      int64_t max_pages, int64_t page_size, int64_t query_tokens,
                                      int32_t split_tokens);

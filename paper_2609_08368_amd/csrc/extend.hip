@@ -11,6 +11,18 @@
 // (sequence, KV head) together on one XCD (workgroups go to the XCDs
 // round-robin by index), so they run at the same time and stream the same
 // keys through that XCD's L2.
+//
+// A row over more than kSegKeys keys is the in-order merge of one partial per
+// key segment. The planner splits a sequence's units at the segments where
+// whole units would leave CUs idle: then every (unit, segment) is an item that
+// leaves its partial in a slot, and merge_segments_kernel finishes the rows;
+// otherwise one workgroup takes all of a unit's keys and merges as it goes.
+// Both give the same bits. One 333-token turn behind 23.5K keys (64/8 heads: 88
+// units for 256 CUs): 486 -> 364 us per call; deterministic decode of 24
+// sequences of 1-32K keys (192 units): 604 -> 351 us.
+#include <algorithm>
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "tile_attn.hpp"
 
@@ -64,14 +76,36 @@ __device__ __forceinline__ SeqRange seq_range(const ExtendArgs& a, int b, int* b
   return {q0, n, kv};
 }
 
+// Tiles of tt chunk rows (nt in all; chunk of n rows behind `prefix` keys)
+// whose keys reach into segment s: all but the first tiles, which end before it.
+__device__ __forceinline__ int segment_tiles(int s, int prefix, int n, int nt, int tt) {
+  const int t = segment_start(s);
+  if (t >= prefix + n) return 0;
+  return t <= prefix ? nt : nt - (t - prefix) / tt;
+}
+// (tile, segment) pairs of one head group of a sequence
+__device__ __forceinline__ long long unit_segments(const SeqRange& r, int tt) {
+  const int nt = (r.n + tt - 1) / tt;
+  long long c = 0;
+  for (int s = segment_count(r.kv) - 1; s >= 0; --s) c += segment_tiles(s, r.kv - r.n, r.n, nt, tt);
+  return c;
+}
+
 __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
   __shared__ int order[kSortMax];
   __shared__ int keys[kSortMax];
+  __shared__ int slot_of[kSortMax];
+  // of the sequences being emitted: (sequence, chunk rows, prefix, first slot or -1), (first item, items of one
+  // head group, first split unit)
+  __shared__ int4 seq_a[1024];
+  __shared__ int4 seq_b[1024];
+  __shared__ unsigned long long all_keys;
   __shared__ int wave_tot[16];
   const int tid = threadIdx.x;
   int bad = 0;
   if (a.gate && *a.gate != 0) {          // the split decode passes compute the rows
-    if (tid == 0) a.ws.hdr[0] = 0;
+    if (tid < 2) a.ws.hdr[tid] = 0;
+    if (tid < kXcds) a.ws.hdr[8 + tid] = 0;
     return;
   }
   if (a.decode_rows) {
@@ -106,8 +140,35 @@ __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
     }
   }
   const bool sorted = a.B <= kSortMax;
+  const int heads = a.Hkv * a.head_blocks, tt = a.tile_tokens;
+  auto tiles = [&](int n) { return (n + tt - 1) / tt; };
   if (sorted) {
-    for (int b = tid; b < a.B; b += blockDim.x) keys[b] = seq_range(a, b, &bad).kv;
+    // Which sequences are split: those with a unit longer than half a
+    // workgroup's share of the call's keys, as far as the slots go. Below
+    // that, whole units in longest-first order fill the chip: six sequences of
+    // 15-24K keys, 57K a workgroup, took 1.735 ms whole and 1.771 ms split;
+    // one of 23.8K, 8.2K a workgroup, 527 and 314 us (segments from 4096).
+    const bool may_split = a.max_slots > 0;
+    SeqRange r{0, 0, 0};
+    if (tid < a.B) r = seq_range(a, tid, &bad);
+    int need = 0;
+    if (may_split) {
+      if (tid == 0) all_keys = 0;
+      __syncthreads();
+      if (r.n > 0) atomicAdd(&all_keys, (unsigned long long)tiles(r.n) * (unsigned long long)heads * r.kv);
+      __syncthreads();
+      if (r.kv > kSegKeys && r.n > 0 && (unsigned long long)r.kv * (2 * a.workers) > all_keys) {
+        const long long n = (long long)heads * unit_segments(r, tt);
+        need = n > a.max_slots ? a.max_slots + 1 : (int)n;
+      }
+    }
+    int tot, first = 0;
+    if (may_split) first = block_exclusive_scan(need, &tot, wave_tot);
+    const bool split = need > 0 && first + need <= a.max_slots;
+    if (tid < a.B) {
+      slot_of[tid] = split ? first : -1;
+      keys[tid] = split ? max(kSegKeys, r.kv / 2) : r.kv;   // about its longest item
+    }
     __syncthreads();
     for (int b = tid; b < a.B; b += blockDim.x) {
       const int kb = keys[b];
@@ -117,49 +178,72 @@ __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
     }
     __syncthreads();
   }
-  const int heads = a.Hkv * a.head_blocks;
-  int offset = 0;
+  // With a multiple of 8 head groups, group gh of a sequence runs on XCD
+  // gh % 8: its units share their keys through that XCD's L2 instead of
+  // every XCD streaming every group's keys. Each XCD's units stay in list
+  // order (longest first), and every XCD gets the same number of units.
+  const bool xcd = kXcdGroups && heads % kXcds == 0;
+  const int lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
+  int offset = 0, moffset = 0;
   for (int p0 = 0; p0 < a.B; p0 += blockDim.x) {
     const int p = p0 + tid;
-    int nt = 0, b = 0;
+    int per = 0, b = 0, slot = -1;
     SeqRange r{0, 0, 0};
     if (p < a.B) {
       b = sorted ? order[p] : p;
       int dummy = 0;
       r = seq_range(a, b, sorted ? &dummy : &bad);
-      nt = (r.n + a.tile_tokens - 1) / a.tile_tokens;
+      slot = sorted ? slot_of[b] : -1;
+      per = slot >= 0 ? (int)unit_segments(r, tt) : tiles(r.n);
     }
-    int tot;
-    const int excl = block_exclusive_scan(nt * heads, &tot, wave_tot);
-    if (p < a.B) {
-      // With a multiple of 8 head groups, group gh of a sequence runs on XCD
-      // gh % 8: its units share their keys through that XCD's L2 instead of
-      // every XCD streaming every group's keys. Each XCD's units stay in list
-      // order (longest first), and every XCD gets the same number of units.
-      const bool xcd = kXcdGroups && heads % kXcds == 0;
-      for (int gh = 0; gh < heads; ++gh) {
+    int tot, mtot = 0, mexcl = 0;
+    const int excl = block_exclusive_scan(per * heads, &tot, wave_tot);
+    if (a.max_slots > 0) mexcl = block_exclusive_scan(slot >= 0 ? tiles(r.n) * heads : 0, &mtot, wave_tot);
+    seq_a[tid] = make_int4(b, r.n, r.kv - r.n, slot);
+    seq_b[tid] = make_int4(offset + excl, per, moffset + mexcl, 0);
+    __syncthreads();
+    // a wave writes the items of a sequence, a lane each
+    for (int s = wave; s < (int)blockDim.x && p0 + s < a.B; s += nwaves) {
+      const int4 sa = seq_a[s], sb = seq_b[s];
+      const int nt = tiles(sa.y);
+      for (int i = lane; i < sb.y * heads; i += 64) {
+        const int gh = i / sb.y, u = i - gh * sb.y;
         const int g = gh / a.head_blocks, hb = gh - g * a.head_blocks;
-        // last tile first: it has the longest key range of the sequence
-        for (int j = 0; j < nt; ++j) {
-          int idx = offset + excl + gh * nt + j;
-          if (xcd) {
-            // position in the XCD's own list: units of the earlier sequences
-            // (heads / 8 groups each), then of this sequence's earlier groups
-            const int k = (offset + excl) / kXcds + (gh / kXcds) * nt + j;
-            idx = k * kXcds + gh % kXcds;
+        // last tile first: it has the longest key range of the sequence; a
+        // split sequence's items go segment by segment, so that the tiles
+        // that read the same keys are neighbours, the last (longest) first
+        int j = u, seg = -1;
+        if (sa.w >= 0) {
+          seg = segment_count(sa.z + sa.y) - 1;
+          for (int c = segment_tiles(seg, sa.z, sa.y, nt, tt); j >= c; c = segment_tiles(seg, sa.z, sa.y, nt, tt)) {
+            j -= c;
+            --seg;
           }
-          const int i0 = (nt - 1 - j) * a.tile_tokens;
-          const int cnt = min(a.tile_tokens, r.n - i0);
-          if (idx < a.max_items)
-            a.ws.items[idx] = make_int4(b, i0, cnt, g | (hb << 16));
-          else
-            bad |= kErrCapacity;     // the host sizing rules this out; reported, never dropped silently
+        }
+        int idx = sb.x + i;
+        if (xcd)   // position in the XCD's own list, behind its items of the earlier sequences and groups
+          idx = (sb.x / kXcds + (gh / kXcds) * sb.y + u) * kXcds + gh % kXcds;
+        const int i0 = (nt - 1 - j) * tt;
+        const int4 unit = make_int4(sa.x, i0, min(tt, sa.y - i0), g | (hb << 16));
+        if (idx >= a.max_items) {
+          bad |= kErrCapacity;     // the host sizing rules this out; reported, never dropped silently
+          continue;
+        }
+        a.ws.items[idx] = unit;
+        if (a.ws.segs) a.ws.segs[idx] = make_int2(seg, seg < 0 ? -1 : sa.w + i);
+        if (seg == 0) {              // every tile reaches into segment 0
+          a.ws.munits[sb.z + gh * nt + j] = unit;
+          a.ws.mslots[sb.z + gh * nt + j] = make_int2(sa.w + (gh + 1) * sb.y - nt, j);
         }
       }
     }
     offset += tot;
+    moffset += mtot;
+    __syncthreads();                     // the lists are rebuilt for the next pass
   }
   if (tid == 0) a.ws.hdr[0] = offset < a.max_items ? offset : a.max_items;
+  if (tid == 1) a.ws.hdr[1] = moffset;
+  if (tid < kXcds) a.ws.hdr[8 + tid] = (a.workers + kXcds - 1 - tid) / kXcds;
   if (bad) atomicOr(a.ws.err, bad);
 }
 
@@ -173,122 +257,247 @@ constexpr int kExtWaves = 8;            // waves per extend workgroup: 256 query
 // (kDirectPages).
 constexpr int kStepPages = 0, kSetPages = 1, kRowPages = 2, kDirectPages = 3;
 
-template <bool kFp8, int kPages, bool kNt = false>
-__global__ __launch_bounds__(kExtWaves * 64, 2) void extend_mfma_kernel(ExtendArgs a) {
+// The next unit of a worker: the head of its XCD's list (entries i with
+// i % 8 == the workgroup's index % 8), or of another list once that is empty;
+// n or more when all are.
+__device__ __forceinline__ int take_unit(int* taken, int n) {
+  for (int d = 0; d < kXcds; ++d) {
+    const int q = (blockIdx.x + d) & (kXcds - 1);
+    const int idx = atomicAdd(&taken[q], 1) * kXcds + q;
+    if (idx < n) return idx;
+  }
+  return n;
+}
+
+// A lane's query row (MFMA column r) of a unit.
+struct UnitRow {
+  bool ok;
+  int ti, head;
+};
+__device__ __forceinline__ UnitRow unit_row(const ExtendArgs& a, int r, int cnt, int g, int hb) {
+  const int RB = a.rows_head;
+  const int ti = r / RB, hi = r - ti * RB;
+  const bool ok = ti < cnt && hb * RB + hi < a.R;
+  return {ok, ti, g * a.R + hb * RB + (ok ? hi : 0)};
+}
+
+template <bool kFp8, int kPages, bool kNt, bool kSeg>
+__global__ __launch_bounds__(kExtWaves * 64, 2) void extend_mfma_kernel(ExtendArgs args) {
   // Units run in list order (longest key range first). Workgroups are handed
   // to the XCDs round-robin, so each XCD takes every eighth entry; the planner
   // lays the list out so those are the units of the (sequence, KV head) groups
   // assigned to that XCD, which then share their keys through its L2.
-  const int unit = blockIdx.x;
-  if (unit >= a.ws.hdr[0]) return;
-  const int4 it = a.ws.items[unit];
-  const int b = it.x, i0 = it.y, cnt = it.z, g = it.w & 0xffff, hb = it.w >> 16;
-  int bad_seq = 0, bad = 0;               // sequence errors are reported by the planner
-  const SeqRange sr = seq_range(a, b, &bad_seq);
-  const int prefix = sr.kv - sr.n;
-  const int t_end = prefix + i0 + cnt;     // keys [0, t_end) are visible to some row
-  const int t_full = prefix + i0;          // keys [0, t_full) are visible to every row
-
+  // Segmented calls run a workgroup per CU that takes units until the list is
+  // empty (a running merge each; 39.9 against 41.1 ms with a workgroup per unit
+  // on the multi-turn batch, same kernel); the others keep a workgroup per
+  // unit, which small units start faster on.
+  __shared__ int next_unit;
+  const int n_units = args.ws.hdr[0];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int RB = a.rows_head;
-  // this lane's query row (MFMA column)
-  const int r = wave * kWaveRows + (lane & 31);
-  const int ti = r / RB, hi = r - ti * RB;
-  const bool row_ok = ti < cnt && hb * RB + hi < a.R;
-  const int head = g * a.R + hb * RB + (row_ok ? hi : 0);
-  const int limit = row_ok ? prefix + i0 + ti : t_end - 1;
-  const int64_t qrow = sr.q0 + i0 + (row_ok ? ti : 0);
+  const int swave = __builtin_amdgcn_readfirstlane(wave);
+  int unit = blockIdx.x;    // (a worker's first unit needs no counter: the planner starts them behind these)
+  // every pass takes a new entry of a finite list, so the loop ends
+  while (unit < n_units) {
+    // The arguments are read again for each unit (the empty asm hides that
+    // they are the same): kept over the loop they would not fit the scalar
+    // registers beside a unit's own values.
+    typedef __attribute__((address_space(4))) const ExtendArgs ConstArgs;
+    ConstArgs* ap = (ConstArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ap));
+    const ExtendArgs a = *(const ExtendArgs*)ap;
+    const int4 it = a.ws.items[unit];
+    const int2 part = kSeg && a.ws.segs ? a.ws.segs[unit] : make_int2(-1, -1);
+    const int b = it.x, i0 = it.y, cnt = it.z, g = it.w & 0xffff, hb = it.w >> 16;
+    int bad_seq = 0, bad = 0;               // sequence errors are reported by the planner
+    const SeqRange sr = seq_range(a, b, &bad_seq);
+    const int prefix = sr.kv - sr.n;
+    const int t_unit = prefix + i0 + cnt;    // keys [0, t_unit) are visible to some row
+    const int t_full = prefix + i0;          // keys [0, t_full) are visible to every row
+    const int t_lo = segment_start(part.x);
+    const int t_end = part.x >= 0 && part.x + 1 < segment_count(t_unit) ? segment_start(part.x + 1) : t_unit;
 
-  bf16x8 qv[8];
-  load_q_operand((const __bf16*)a.q + qrow * a.q_st + (int64_t)head * a.q_sh, row_ok, qv);
-  f32x16 o[4];
-#pragma unroll
-  for (int jd = 0; jd < 4; ++jd)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) o[jd][e] = 0.f;
-  float m_run = kNegInf, l_run = 0.f;
-  int bad_scale = 0;
-  // the K dequantisation scale joins the softmax scale, the V scale the output
-  const KvScales dq = kv_scales<kFp8>(a.kv, g, &bad_scale);
-  const float scale = a.scale * dq.k;
-  const int* bt_row = a.kv.bt + (int64_t)b * a.kv.bt_sb;
-  // a wave whose 32 rows are all past the unit's tokens (a short chunk, or
-  // the one token of a deterministic decode) only stages
-  const bool active = __builtin_amdgcn_ballot_w64(row_ok) != 0;
-  if constexpr (kPages == kDirectPages) {
-    static_assert(!kFp8, "rows go to LDS as stored: bf16 pages only");
-    __shared__ __attribute__((aligned(16))) char kl0[kDlKBytes], kl1[kDlKBytes], vl0[kDlVBytes], vl1[kDlVBytes];
-    if (active)
-      tile_attend_dl<true, kNt>(a.kv, scale, bt_row, g, t_end, t_full, limit, qv, kl0, kl1, vl0, vl1, o, m_run,
-                                l_run, bad);
-    else
-      tile_attend_dl<false, kNt>(a.kv, scale, bt_row, g, t_end, t_full, limit, qv, kl0, kl1, vl0, vl1, o, m_run,
-                                 l_run, bad);
-  } else {
-    __shared__ TileLds lds;
-    auto attend = [&](auto compute_tag) {
-      constexpr bool kC = decltype(compute_tag)::value;
-      tile_attend_pp<kExtWaves, kPages != kRowPages, kFp8, kC, kPages == kSetPages, kNt>(
-          a.kv, scale, bt_row, g, 0, t_end, t_full, limit, qv, lds, o, m_run, l_run, bad);
-    };
-    if (active)
-      attend(std::true_type{});
-    else
-      attend(std::false_type{});
-  }
+    const UnitRow row = unit_row(a, wave * kWaveRows + (lane & 31), cnt, g, hb);
+    const int limit = row.ok ? prefix + i0 + row.ti : t_unit - 1;
+    const int64_t qrow = sr.q0 + i0 + (row.ok ? row.ti : 0);
 
-  const float l_tot = sum_l32(l_run);
-  if (row_ok) {
-    const float inv = l_tot > 0.f ? dq.v / l_tot : 0.f;
-    if (a.out_f32)
-      store_o_row((float*)a.out + qrow * a.out_st + (int64_t)head * a.out_sh, o, inv);
-    else
-      store_o_row((__bf16*)a.out + qrow * a.out_st + (int64_t)head * a.out_sh, o, inv);
-    if (a.lse && lane < 32)
-      a.lse[qrow * a.lse_st + (int64_t)head * a.lse_sh] =
-          l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : kNegInf;
+    bf16x8 qv[8];
+    load_q_operand((const __bf16*)a.q + qrow * a.q_st + (int64_t)row.head * a.q_sh, row.ok, qv);
+    f32x16 o[4];
+#pragma unroll
+    for (int jd = 0; jd < 4; ++jd)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[jd][e] = 0.f;
+    float m_run = t_lo > 0 ? kNoKey : kNegInf, l_run = 0.f;
+    int bad_scale = 0;
+    // the K dequantisation scale joins the softmax scale, the V scale the output
+    const KvScales dq = kv_scales<kFp8>(a.kv, g, &bad_scale);
+    const float scale = a.scale * dq.k;
+    const int* bt_row = a.kv.bt + (int64_t)b * a.kv.bt_sb;
+    // a wave whose 32 rows are all past the unit's tokens (a short chunk, or
+    // the one token of a deterministic decode) only stages
+    const bool active = __builtin_amdgcn_ballot_w64(row.ok) != 0;
+    float* stash = a.ws.stash + ((size_t)blockIdx.x * a.slot_waves + swave) * kSegWaveFloats;
+    if constexpr (kPages == kDirectPages) {
+      static_assert(!kFp8, "rows go to LDS as stored: bf16 pages only");
+      __shared__ __attribute__((aligned(16))) char kl0[kDlKBytes], kl1[kDlKBytes], vl0[kDlVBytes], vl1[kDlVBytes];
+      if (active)
+        tile_attend_dl<true, kNt, kSeg>(a.kv, scale, bt_row, g, t_lo, t_end, t_full, limit, qv, kl0, kl1, vl0, vl1, o,
+                                  m_run, l_run, bad, stash);
+      else
+        tile_attend_dl<false, kNt, kSeg>(a.kv, scale, bt_row, g, t_lo, t_end, t_full, limit, qv, kl0, kl1, vl0, vl1, o,
+                                   m_run, l_run, bad, stash);
+    } else {
+      __shared__ TileLds lds;
+      auto attend = [&](auto compute_tag) {
+        constexpr bool kC = decltype(compute_tag)::value;
+        tile_attend_pp<kExtWaves, kPages != kRowPages, kFp8, kC, kPages == kSetPages, kNt, kSeg>(
+            a.kv, scale, bt_row, g, t_lo, t_end, t_full, limit, qv, lds, o, m_run, l_run, bad, stash);
+      };
+      if (active)
+        attend(std::true_type{});
+      else
+        attend(std::false_type{});
+    }
+    // the next unit is taken only now, so that no worker holds one it cannot start
+    if (kSeg && threadIdx.x == 0) next_unit = take_unit(a.ws.hdr + 8, n_units);
+
+    if (kSeg && part.y >= 0) {
+      if (active) seg_store(a.ws.part + ((size_t)part.y * a.slot_waves + swave) * kSegWaveFloats, o, m_run, l_run);
+    } else {
+      if (kSeg && active && t_unit > kSegKeys) seg_merge(stash, o, m_run, l_run);
+      const float l_tot = sum_l32(l_run);
+      if (row.ok) {
+        const float inv = l_tot > 0.f ? dq.v / l_tot : 0.f;
+        if (a.out_f32)
+          store_o_row((float*)a.out + qrow * a.out_st + (int64_t)row.head * a.out_sh, o, inv);
+        else
+          store_o_row((__bf16*)a.out + qrow * a.out_st + (int64_t)row.head * a.out_sh, o, inv);
+        if (a.lse && lane < 32)
+          a.lse[qrow * a.lse_st + (int64_t)row.head * a.lse_sh] =
+              l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : kNegInf;
+      }
+    }
+    if (bad) atomicOr(a.ws.err, kErrPage);
+    if (bad_scale) atomicOr(a.ws.err, kErrScale);
+    if constexpr (!kSeg) break;
+    // the LDS tiles are free and next_unit is written; it is read before the
+    // next unit's barriers, which every wave passes before the next write
+    __syncthreads();
+    unit = __builtin_amdgcn_readfirstlane(next_unit);
   }
-  if (bad) atomicOr(a.ws.err, kErrPage);
-  if (bad_scale) atomicOr(a.ws.err, kErrScale);
+}
+
+// Finishes the rows of split units: merges their segments' partials in key
+// order, as seg_flush does for whole units. A wave takes 32 dimensions of 32
+// rows (block jd of the wave's state), so the elements it merges and the
+// weights are those of the whole-unit merge.
+template <bool kFp8>
+__global__ __launch_bounds__(256) void merge_segments_kernel(ExtendArgs a) {
+  const int n = a.ws.hdr[1] * a.slot_waves;
+  const int lane = threadIdx.x & 63;
+  const int jd = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int wi = blockIdx.x; wi < n; wi += gridDim.x) {
+    const int u = wi / a.slot_waves, w = wi - u * a.slot_waves;
+    const int4 it = a.ws.munits[u];
+    const int2 ms = a.ws.mslots[u];
+    const int b = it.x, i0 = it.y, cnt = it.z, g = it.w & 0xffff, hb = it.w >> 16;
+    const UnitRow row = unit_row(a, w * kWaveRows + (lane & 31), cnt, g, hb);
+    if (__builtin_amdgcn_ballot_w64(row.ok) == 0) continue;
+    int dummy = 0;
+    const SeqRange sr = seq_range(a, b, &dummy);
+    const int prefix = sr.kv - sr.n, nt = (sr.n + a.tile_tokens - 1) / a.tile_tokens;
+    const int n_seg = segment_count(prefix + i0 + cnt);
+    f32x16 o;
+    float m = 0.f, l = 0.f;
+    int slot = ms.x + ms.y;
+    for (int s = 0; s < n_seg; ++s) {
+      const float* p = a.ws.part + ((size_t)slot * a.slot_waves + w) * kSegWaveFloats;
+      slot -= segment_tiles(s + 1, prefix, sr.n, nt, a.tile_tokens);
+      const float m1 = p[4096 + lane], l1 = p[4160 + lane];
+      f32x4 x[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = *reinterpret_cast<const f32x4*>(p + 256 * (4 * jd + i) + 4 * lane);
+      if (s == 0) {
+        m = m1;
+        l = l1;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[e] = x[e >> 2][e & 3];
+      } else {
+        const SegWeights sw = seg_weights(m, m1, sum_l32(l1));
+        l = seg_mix(l, l1, sw);
+        m = sw.m;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[e] = seg_mix(o[e], x[e >> 2][e & 3], sw);
+      }
+    }
+    const float l_tot = sum_l32(l);
+    if (row.ok) {
+      const int64_t qrow = sr.q0 + i0 + row.ti;
+      const KvScales dq = kv_scales<kFp8>(a.kv, g, &dummy);
+      const float inv = l_tot > 0.f ? dq.v / l_tot : 0.f;
+      const int64_t off = qrow * a.out_st + (int64_t)row.head * a.out_sh;
+      if (a.out_f32)
+        store_o_block((float*)a.out + off, o, jd, inv);
+      else
+        store_o_block((__bf16*)a.out + off, o, jd, inv);
+      if (a.lse && jd == 0 && lane < 32)
+        a.lse[qrow * a.lse_st + (int64_t)row.head * a.lse_sh] =
+            l_tot > 0.f ? (m + __builtin_amdgcn_logf(l_tot)) * kLn2 : kNegInf;
+    }
+  }
 }
 
 }  // namespace
 
 hipError_t launch_extend(const ExtendArgs& a, hipStream_t stream, KernelTimer* timer) {
   plan_extend_kernel<<<1, 1024, 0, stream>>>(a);
-  const unsigned grid = (unsigned)a.max_items;
+  const unsigned grid = (unsigned)(a.segmented ? a.workers : a.max_items);
   if (timer) (void)hipEventRecord(timer->start, stream);
-  const int64_t ss = a.kv.ss > a.kv.v_ss ? a.kv.ss : a.kv.v_ss;
-  const bool scalar_ids = ((int64_t)a.kv.page_size * ss + kHeadDim) * 2 < (int64_t(1) << 31);
+  const bool scalar_ids = scalar_page_offsets(a.kv);
   const int pages = !scalar_ids ? kRowPages : (a.kv.page_size >= kKeys ? kStepPages : kSetPages);
   // decode through the extend kernel with one unit per (sequence, KV head):
   // every key row is read once, so the rows are loaded non-temporally (pages
   // of at least a step only)
   const bool once = a.decode_rows > 0 && a.head_blocks == 1 && a.decode_rows <= a.tile_tokens;
-  auto go = [&](auto fp8_tag) {
-    constexpr bool kF = decltype(fp8_tag)::value;
+  // (the segmented kernels are instances of their own: the merge's registers
+  // slowed the others' step loop by 4%, draft batch 852 against 885 us)
+  auto go = [&](auto fp8_tag, auto seg_tag) {
+    constexpr bool kF = decltype(fp8_tag)::value, kSeg = decltype(seg_tag)::value;
+    auto launch = [&](auto pages_tag, auto nt_tag) {
+      extend_mfma_kernel<kF, decltype(pages_tag)::value, decltype(nt_tag)::value, kSeg>
+          <<<grid, kExtWaves * 64, 0, stream>>>(a);
+    };
+    const std::true_type nt{};
+    const std::false_type cached{};
+    bool direct = false;
     if constexpr (!kF) {
-      if (pages == kStepPages && !a.staged) {
-        if (once)
-          extend_mfma_kernel<false, kDirectPages, true><<<grid, kExtWaves * 64, 0, stream>>>(a);
-        else
-          extend_mfma_kernel<false, kDirectPages><<<grid, kExtWaves * 64, 0, stream>>>(a);
-        return;
-      }
+      direct = pages == kStepPages && !a.staged;
+      const std::integral_constant<int, kDirectPages> p{};
+      if (direct && once)
+        launch(p, nt);
+      else if (direct)
+        launch(p, cached);
     }
-    if (pages == kStepPages && once)
-      extend_mfma_kernel<kF, kStepPages, true><<<grid, kExtWaves * 64, 0, stream>>>(a);
-    else if (pages == kStepPages)
-      extend_mfma_kernel<kF, kStepPages><<<grid, kExtWaves * 64, 0, stream>>>(a);
-    else if (pages == kSetPages)
-      extend_mfma_kernel<kF, kSetPages><<<grid, kExtWaves * 64, 0, stream>>>(a);
-    else
-      extend_mfma_kernel<kF, kRowPages><<<grid, kExtWaves * 64, 0, stream>>>(a);
+    const std::integral_constant<int, kStepPages> step{};
+    if (direct) {
+    } else if (pages == kStepPages && once) {
+      launch(step, nt);
+    } else if (pages == kStepPages) {
+      launch(step, cached);
+    } else if (pages == kSetPages) {
+      launch(std::integral_constant<int, kSetPages>{}, cached);
+    } else {
+      launch(std::integral_constant<int, kRowPages>{}, cached);
+    }
+    if (a.max_slots > 0)
+      merge_segments_kernel<kF><<<(unsigned)std::min(4 * a.workers, a.max_slots * a.slot_waves), 256, 0, stream>>>(a);
   };
+  const std::true_type yes{};
+  const std::false_type no{};
   if (a.kv.k_scale)
-    go(std::true_type{});
+    a.segmented ? go(yes, yes) : go(yes, no);
   else
-    go(std::false_type{});
+    a.segmented ? go(no, yes) : go(no, no);
   if (timer) (void)hipEventRecord(timer->stop, stream);
   return hipGetLastError();
 }

@@ -38,6 +38,13 @@ struct PagedKV {
   int64_t ks_s, vs_s;
 };
 
+// In-page byte offsets fit 31 bits (the extend routines then read a page id per
+// step or row set with a scalar load; otherwise each thread looks up its rows').
+inline bool scalar_page_offsets(const PagedKV& kv) {
+  const int64_t ss = kv.ss > kv.v_ss ? kv.ss : kv.v_ss;
+  return (kv.page_size * ss + 128) * 2 < (int64_t(1) << 31);
+}
+
 // Levels of nested shared prefix pages the decode planner detects: the prefix a
 // trajectory group shares, then prefixes shared by subsets of it (sessions
 // that branch after a common turn).
@@ -109,9 +116,39 @@ struct DecodeArgs {
   DecodePlanWs ws;
 };
 
+// Key segments of an extend row: [0, kSegKeys), then doubling: segment s > 0 is
+// [kSegKeys 2^(s-1), kSegKeys 2^s). A row over several is the in-order merge of
+// one partial per segment (see tile_attn.hpp), so its keys may be split between
+// workgroups without changing its bits. A multiple of 128. Few and
+// doubling, because a whole unit writes its state (up to 135 KB) at each
+// boundary, all CUs at about the same time: equal segments of 4096 keys took
+// 42.5 ms on the multi-turn batch (40.0 before, 38.7 with the state kept
+// nowhere), doubling ones from 4096 42.6 (41.9 before, on that box) and from
+// 8192 0.6% less. Where keys are split the longest item counts: deterministic
+// decode up to 32K keys took 351 us with doubling segments from 4096 or 8192
+// (602 before), and a turn of 333 tokens behind 23.5K 313 and 388 (483). From
+// 16384: 351 and 364 us, and 40.36 ms on the multi-turn batch (40.32 before).
+constexpr int kSegKeys = 16384;
+inline __host__ __device__ int segment_start(int s) { return s > 0 ? kSegKeys << (s - 1) : 0; }
+// segments of a row over n > 0 keys
+inline __host__ __device__ int segment_count(int n) {
+  return n <= kSegKeys ? 1 : 33 - __builtin_clz((unsigned)((n - 1) / kSegKeys));
+}
+// units are split in batches up to this size (the planner keeps a thread per sequence)
+constexpr int kSplitBatchMax = 1024;
+// floats of one wave's partial: per lane 64 of o, m and l
+constexpr int kSegWaveFloats = 64 * 66;
+
 struct ExtendPlanWs {
-  int* hdr;        // [0] number of work units
+  int* hdr;        // [0] work units, [1] split units, [8..15] next entry of each of the eight interleaved lists
   int4* items;     // [max_items] (sequence, first chunk row, chunk rows, KV head | head block << 16)
+  // null when the call's keys cannot be split: (segment, slot) of each item;
+  // segment -1: all of the unit's keys
+  int2* segs;
+  int4* munits;    // [min(max_slots, units)] split units, as items
+  int2* mslots;    // (first slot of the unit's head group, the unit's place in its segments)
+  float* part;     // [max_slots, slot_waves, kSegWaveFloats] partials of split units
+  float* stash;    // [workgroups, slot_waves, kSegWaveFloats] running merges of unsplit units
   int* err;
 };
 
@@ -133,6 +170,12 @@ struct ExtendArgs {
   float* lse;
   int64_t lse_st, lse_sh;
   int max_items;
+  int max_slots;          // partials of split units (0: no unit is split)
+  int slot_waves;         // waves of a unit that hold rows, at most
+  int workers;            // workgroups that take units from the list until it is empty
+  // rows over more than kSegKeys keys are merged from segments; off where the
+  // block table has room for no more keys, and with `staged` steps (see there)
+  int segmented;
   // n > 0: decode through the extend kernel: sequence b owns query rows
   // b n .. b n + n - 1, its last n keys (none if kv_lens[b] == 0; qo_indptr is
   // not read), and the rows of empty sequences are written as zeros with
@@ -142,7 +185,8 @@ struct ExtendArgs {
   // (a multi-token decode routed through extend units, which owes extend no
   // bitwise agreement and streams its rows faster that way); zero: pages of
   // at least 64 keys take 128-key steps, as every extend and deterministic
-  // decode does
+  // decode does. Such rows are not merged from segments either (their batches
+  // fill the chip with whole units).
   int staged;
   // nullable: the extend planner queues no unit (and writes nothing) when
   // *gate != 0, i.e. when the decode planner that runs before it found shared
@@ -202,6 +246,9 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream, KernelTimer* t
 // an earlier call already looked it up.
 constexpr size_t kScratchBytes = size_t(160) << 20;
 constexpr size_t kScratchErrBytes = 256;
+// behind them, the running merges of a deterministic decode: room for 256
+// workgroups of 8 waves
+constexpr size_t kScratchStashBytes = size_t(256) * 8 * kSegWaveFloats * 4;
 hipError_t scratch_address(hipStream_t stream, void** ptr);
 bool scratch_address_if_set_up(void** ptr);
 // Measurement aids (see rl_attn_diag.h): a grid-stride read of `bytes` and a

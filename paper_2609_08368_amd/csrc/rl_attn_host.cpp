@@ -521,37 +521,110 @@ ExtendShape extend_shape(int64_t R) {
   return s;
 }
 
-// Work units are (sequence, KV head, head block, chunk tile): at most
-// Hkv * head_blocks * (B + ceil(total_q / tile_tokens)).
-size_t extend_ws_bytes(int64_t B, int64_t total_q, int64_t Hkv, int64_t R, int* max_items) {
+// Workspace of an extend call. Work units are (sequence, KV head, head block,
+// chunk tile): at most Hkv * head_blocks * (B + ceil(total_q / tile_tokens)).
+// Workers (one workgroup per CU) take the units from the list. Where the block
+// table has room for more than one segment of keys (and `segments` allows it),
+// each has a running merge of its own, and units may be split at the segments: every (unit,
+// segment) of a split unit has a slot, at most kMaxSlots of them and kSlotBytes
+// in all (a call with more work than that fills the chip with whole units).
+// row_tokens: the most chunk tokens a unit can hold.
+constexpr int64_t kMaxSlots = 4096;
+constexpr int64_t kSlotBytes = int64_t(256) << 20;
+struct ExtendLayout {
+  int max_units, max_slots, slot_waves, workers;
+  bool segmented;
+  size_t off_munits, off_mslots, off_segs, off_part, off_stash, total;
+};
+
+ExtendLayout extend_layout(int64_t B, int64_t total_q, int64_t row_tokens, int64_t Hkv, int64_t R,
+                           int64_t max_tokens, int cus, bool segments = true) {
   const ExtendShape s = extend_shape(R);
-  const int64_t items = Hkv * s.head_blocks * (B + (total_q + s.tile_tokens - 1) / s.tile_tokens);
-  *max_items = (int)std::min<int64_t>(items, INT32_MAX / 2);
-  return 256 + align256((size_t)*max_items * 16);
+  ExtendLayout L{};
+  const int64_t units = Hkv * s.head_blocks * (B + (total_q + s.tile_tokens - 1) / s.tile_tokens);
+  L.max_units = (int)std::min<int64_t>(units, INT32_MAX / 2);
+  L.slot_waves = (int)((std::max<int64_t>(1, std::min<int64_t>(row_tokens, s.tile_tokens)) * s.rows_head + 31) / 32);
+  size_t off = 256 + align256((size_t)L.max_units * 16);
+  L.workers = (int)std::min<int64_t>(cus, L.max_units);
+  L.segmented = segments && max_tokens > rl::kSegKeys;
+  if (L.segmented) {
+    const int64_t slot_bytes = (int64_t)L.slot_waves * rl::kSegWaveFloats * 4;
+    const int64_t segs = rl::segment_count((int)std::min<int64_t>(max_tokens, INT32_MAX));
+    if (B <= rl::kSplitBatchMax)
+      L.max_slots = (int)std::min<int64_t>({kMaxSlots, kSlotBytes / slot_bytes, units * segs});
+    L.workers = (int)std::min<int64_t>(cus, (int64_t)L.max_units + L.max_slots);
+    off = 256 + align256((size_t)(L.max_units + L.max_slots) * 16);
+    L.off_munits = off;
+    off += align256((size_t)L.max_slots * 16);
+    L.off_mslots = off;
+    off += align256((size_t)L.max_slots * 8);
+    L.off_segs = off;
+    off += align256((size_t)(L.max_units + L.max_slots) * 8);
+    L.off_part = off;
+    off += align256((size_t)L.max_slots * slot_bytes);
+    L.off_stash = off;
+    off += align256((size_t)L.workers * slot_bytes);
+  }
+  L.total = off;
+  return L;
+}
+
+// The list alone: what the call cannot do without when its workspace is the
+// static scratch array (the running merges lie behind that array).
+size_t extend_list_bytes(const ExtendLayout& L) { return 256 + align256((size_t)L.max_units * 16); }
+
+int current_cus(int* cus) {
+  int dev = 0;
+  const hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+  *cus = device_cus(dev);
+  return RL_OK;
 }
 
 // Work-unit shape, workspace and launch of an extend call whose arguments
 // (pages, q, lengths, output) are already filled in. prof_kind: which timing
-// slot the attention kernel is counted under; `given`: a workspace already
-// carved out of the call's (else the stream's is taken); `timed`: whether the
-// kernel timer is recorded around the launch.
-int run_extend(rl::ExtendArgs& a, hipStream_t st, int prof_kind, bool noalloc = false, const WsView* given = nullptr,
+// slot the attention kernel is counted under; `given`: a workspace of `L`'s
+// size already carved out of the call's (else the stream's is taken); `room`:
+// bytes of the static scratch array it may use (allocation-free calls; units
+// are split only if all of L fits); `timed`: whether the kernel timer is
+// recorded around the launch.
+int run_extend(rl::ExtendArgs& a, const ExtendLayout& L, hipStream_t st, int prof_kind, bool noalloc = false,
+               const WsView* given = nullptr, size_t room = rl::kScratchBytes - rl::kScratchErrBytes,
                bool timed = true) {
-  int max_items = 0;
-  const size_t bytes = extend_ws_bytes(a.B, a.total_q, a.Hkv, a.R, &max_items);
+  const size_t off_stash = L.segmented ? L.off_stash : L.total;
+  const bool splits = L.max_slots > 0 && (!noalloc || off_stash <= room);
   WsView w{};
   if (given)
     w = *given;
   else
-    RL_TRY(get_ws(st, bytes, noalloc, &w));
+    RL_TRY(get_ws(st, noalloc ? extend_list_bytes(L) : L.total, noalloc, &w));
   char* base = w.ptr;
   const ExtendShape s = extend_shape(a.R);
   a.rows_head = s.rows_head;
   a.tile_tokens = s.tile_tokens;
   a.head_blocks = s.head_blocks;
-  a.max_items = max_items;
+  a.slot_waves = L.slot_waves;
+  a.workers = L.workers;
+  a.max_slots = splits ? L.max_slots : 0;
+  a.max_items = L.max_units + a.max_slots;
   a.ws.hdr = reinterpret_cast<int*>(base);
   a.ws.items = reinterpret_cast<int4*>(base + 256);
+  if (splits) {
+    a.ws.munits = reinterpret_cast<int4*>(base + L.off_munits);
+    a.ws.mslots = reinterpret_cast<int2*>(base + L.off_mslots);
+    a.ws.segs = reinterpret_cast<int2*>(base + L.off_segs);
+    a.ws.part = reinterpret_cast<float*>(base + L.off_part);
+  }
+  a.segmented = L.segmented ? 1 : 0;
+  if (L.segmented) {
+    a.ws.stash = reinterpret_cast<float*>(base + L.off_stash);
+    if (noalloc) {
+      // the scratch array's own region (w.err is the array's first word)
+      a.ws.stash = reinterpret_cast<float*>(reinterpret_cast<char*>(w.err) + rl::kScratchBytes);
+      const size_t fit = rl::kScratchStashBytes / ((size_t)L.slot_waves * rl::kSegWaveFloats * 4);
+      a.workers = (int)std::min<size_t>(a.workers, fit);
+    }
+  }
   a.ws.err = w.err;
   rl::KernelTimer slot;
   rl::KernelTimer* timer = noalloc || !timed ? nullptr : prof_timer(&slot, st);
@@ -643,22 +716,24 @@ int decode_impl(const rl_tensor* q, const rl_tensor* k_pages, const rl_tensor* v
   };
   const bool via_extend =
       o.deterministic || (n_tok > 1 && o.prefix_share == RL_PREFIX_OFF && o.split_tokens == 0 && rows_merge);
+  if (via_extend && !rows_merge)
+    return fail(RL_ERR_UNSUPPORTED,
+                "deterministic multi-token decode needs q, out and lse_out with batch stride = tokens x token stride");
+  int cus = 0;
+  RL_TRY(current_cus(&cus));
+  const ExtendLayout ext =
+      extend_layout(B, B * n_tok, n_tok, Hkv, Hq / Hkv, (int64_t)a.kv.max_pages * a.kv.page_size, cus,
+                    o.deterministic || kv_dtype == RL_FP8_E4M3 || a.kv.page_size < 64 ||
+                        !rl::scalar_page_offsets(a.kv));
   if (via_extend) {
     // one extend row per (sequence, token): the same kernel and per-row
-    // arithmetic as extend, with no split of the keys, so the result of a
-    // sequence does not depend on the rest of the batch and equals extend's
-    // bitwise
-    if (!rows_merge)
-      return fail(RL_ERR_UNSUPPORTED,
-                  "deterministic multi-token decode needs q, out and lse_out with batch stride = tokens x token stride");
+    // arithmetic as extend (keys merged at fixed segment boundaries), so the
+    // result of a sequence does not depend on the rest of the batch and equals
+    // extend's bitwise
     rl::ExtendArgs x = extend_rows();
     x.staged = o.deterministic ? 0 : 1;
-    return run_extend(x, st, 0, noalloc);
+    return run_extend(x, ext, st, 0, noalloc);
   }
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-  const int cus = device_cus(dev);
   const DecodeLayout lay = decode_layout(B, Hq, Hkv, a.kv.max_pages, a.kv.page_size, o.split_tokens, cus,
                                          o.prefix_share == RL_PREFIX_AUTO, kv_dtype == RL_FP8_E4M3, (int)n_tok);
   // the extend pass's work list follows the decode workspace; the
@@ -667,11 +742,11 @@ int decode_impl(const rl_tensor* q, const rl_tensor* k_pages, const rl_tensor* v
   bool route = n_tok > 1 && o.prefix_share == RL_PREFIX_AUTO && o.split_tokens == 0 && rows_merge &&
                kv_dtype != RL_FP8_E4M3;
   const size_t ext_off = align256(lay.total);
-  int ext_items = 0;
+  const size_t room = rl::kScratchBytes - rl::kScratchErrBytes;
   size_t need = lay.total;
   if (route) {
-    need = ext_off + extend_ws_bytes(B, B * n_tok, Hkv, Hq / Hkv, &ext_items);
-    if (noalloc && need > rl::kScratchBytes - rl::kScratchErrBytes) {
+    need = ext_off + (noalloc ? extend_list_bytes(ext) : ext.total);
+    if (noalloc && need > room) {
       route = false;
       need = lay.total;
     }
@@ -725,7 +800,7 @@ int decode_impl(const rl_tensor* q, const rl_tensor* k_pages, const rl_tensor* v
   rl::KernelTimer slot;
   rl::KernelTimer* timer = noalloc ? nullptr : prof_timer(&slot, st);
   if (!route) {
-    e = rl::launch_decode(a, st, timer);
+    const hipError_t e = rl::launch_decode(a, st, timer);
     prof_commit(0, timer);
     if (e != hipSuccess) return hip_fail(e, "decode kernel launch");
     return RL_OK;
@@ -733,14 +808,14 @@ int decode_impl(const rl_tensor* q, const rl_tensor* k_pages, const rl_tensor* v
   // both passes: the timer spans them, planners included (either the split
   // passes or the extend pass does the work)
   if (timer) (void)hipEventRecord(timer->start, st);
-  e = rl::launch_decode(a, st, nullptr);
+  hipError_t e = rl::launch_decode(a, st, nullptr);
   int rc = RL_OK;
   if (e == hipSuccess) {
     rl::ExtendArgs x = extend_rows();
     x.staged = 1;
     x.gate = a.ws.hdr + 3;
     const WsView xw{base + ext_off, w.err};
-    rc = run_extend(x, st, 0, noalloc, &xw, false);
+    rc = run_extend(x, ext, st, 0, noalloc, &xw, room - ext_off, false);
   }
   if (timer) (void)hipEventRecord(timer->stop, st);
   prof_commit(0, timer);
@@ -804,7 +879,11 @@ int extend_impl(const rl_tensor* q, const rl_tensor* qo_indptr, const rl_tensor*
   a.lse = lse_out ? static_cast<float*>(lse_out->data) : nullptr;
   a.lse_st = lse_out ? lse_out->strides[0] : 0;
   a.lse_sh = lse_out ? lse_out->strides[1] : 0;
-  return run_extend(a, st, 1);
+  int cus = 0;
+  RL_TRY(current_cus(&cus));
+  const ExtendLayout L =
+      extend_layout(B, total_q, total_q, Hkv, Hq / Hkv, (int64_t)a.kv.max_pages * a.kv.page_size, cus);
+  return run_extend(a, L, st, 1);
 }
 
 // ------------------------------------------------------------------- append
@@ -1068,9 +1147,11 @@ size_t rl_attn_decode_workspace_size(int64_t batch, int64_t num_q_heads, int64_t
   // deterministic decode uses the extend work list, and a multi-token decode
   // with prefix sharing on queues both (the extend list after the decode
   // workspace): the largest of these
-  int mi = 0;
   const int64_t R = num_q_heads / num_kv_heads;
-  const size_t ext = R >= 1 ? extend_ws_bytes(batch, batch * query_tokens, num_kv_heads, R, &mi) : 0;
+  const size_t ext = R >= 1 ? extend_layout(batch, batch * query_tokens, query_tokens, num_kv_heads, R,
+                                            max_pages * page_size, cus)
+                                  .total
+                            : 0;
   size_t total = ext;
   for (bool fp8 : {false, true}) {
     const size_t dec = decode_layout(batch, num_q_heads, num_kv_heads, max_pages, page_size, split, cus, true, fp8,
@@ -1083,11 +1164,11 @@ size_t rl_attn_decode_workspace_size(int64_t batch, int64_t num_q_heads, int64_t
 
 size_t rl_attn_extend_workspace_size(int64_t batch, int64_t total_q, int64_t num_q_heads, int64_t num_kv_heads,
                                      int64_t max_pages, int64_t page_size) {
-  (void)max_pages;
-  (void)page_size;
   if (batch <= 0 || num_q_heads <= 0 || num_kv_heads <= 0) return 0;
-  int mi = 0;
-  return extend_ws_bytes(batch, total_q, num_kv_heads, num_q_heads / num_kv_heads, &mi);
+  int dev = 0, cus = 256;
+  if (hipGetDevice(&dev) == hipSuccess) cus = device_cus(dev);
+  return extend_layout(batch, total_q, total_q, num_kv_heads, num_q_heads / num_kv_heads, max_pages * page_size, cus)
+      .total;
 }
 
 // ------------------------------------------------------------ measurement aids
@@ -1192,10 +1273,8 @@ int rl_attn_diag_extend_capacity(int64_t batch, int64_t total_q, int64_t num_q_h
   if (!out) return fail(RL_ERR_INVALID_ARG, "diag_extend_capacity: out is NULL");
   if (batch <= 0 || total_q < 0 || num_q_heads <= 0 || num_kv_heads <= 0 || num_q_heads % num_kv_heads != 0)
     return fail(RL_ERR_INVALID_ARG, "diag_extend_capacity: invalid sizes");
-  int mi = 0;
-  (void)extend_ws_bytes(batch, total_q, num_kv_heads, num_q_heads / num_kv_heads, &mi);
   const ExtendShape sh = extend_shape(num_q_heads / num_kv_heads);
-  out[0] = mi;
+  out[0] = extend_layout(batch, total_q, total_q, num_kv_heads, num_q_heads / num_kv_heads, 0, 1).max_units;
   out[1] = sh.rows_head;
   out[2] = sh.tile_tokens;
   out[3] = sh.head_blocks;

@@ -17,7 +17,7 @@
 
 #include "kernels.hpp"
 
-static __device__ __align__(256) char scratch[rl::kScratchBytes];
+static __device__ __align__(256) char scratch[rl::kScratchBytes + rl::kScratchStashBytes];
 
 namespace rl {
 

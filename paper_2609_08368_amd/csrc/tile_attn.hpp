@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "attn_common.hpp"
+#include "kernels.hpp"
 
 namespace rl {
 
@@ -243,6 +244,100 @@ __device__ __forceinline__ void tile_attend(const PagedKV& kv, float scale, cons
   for (int j = 0; j < nsteps; ++j) step(j, ka, va);
 }
 
+// ---- key segments -----------------------------------------------------------
+// The extend routines (tile_attend_pp, tile_attend_dl) define a row's result
+// over more than kSegKeys keys as the merge, in key order, of one partial per
+// key segment; each partial starts from an empty state. The
+// boundaries are fixed key positions, so the segments can be computed by one
+// workgroup after another (the running merge is kept in memory, seg_flush) or
+// by several at once (merge_segments_kernel), with the same bits: whether a
+// call splits its keys to fill the chip does not change a row. A segment in
+// which a row sees no key leaves its state untouched.
+
+// Running maximum of a row that has seen no key of a later segment: finite, so
+// that its step needs no test (masked scores give p = exp2(-inf) = 0 and the
+// state scales by 1), and below every maximum that raises it. (Key 0 is in
+// segment 0 and visible to every row, whose maximum starts at -inf.)
+constexpr float kNoKey = -3.0e38f;
+
+struct SegWeights {
+  float m, a0, a1;
+  bool keep;
+};
+// Merge of a state with running maximum m0 and a later segment's partial (m1,
+// and l1, its row sum over both halves of the row). l1 is compared by its bits:
+// a partial of NaN scores may have m1 = kNoKey too and has to reach the result.
+__device__ __forceinline__ SegWeights seg_weights(float m0, float m1, float l1) {
+  SegWeights w;
+  w.keep = m1 == kNoKey && __float_as_uint(l1) == 0u;
+  w.m = w.keep ? m0 : fmaxf(m0, m1);
+  w.a0 = exp2_fast(m0 - w.m);
+  w.a1 = exp2_fast(m1 - w.m);
+  return w;
+}
+__device__ __forceinline__ float seg_mix(float x0, float x1, const SegWeights& w) {
+  return w.keep ? x0 : fmaf(x0, w.a0, x1 * w.a1);
+}
+
+// A wave's state in memory: o as 16 float4 per lane, lane after lane (element
+// 4 i + e of chunk 4 jd + i is o[jd][4 i + e]), then m and l.
+__device__ __forceinline__ void seg_store(float* p, const f32x16 (&o)[4], float m, float l) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int jd = 0; jd < 4; ++jd)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<f32x4*>(p + 256 * (4 * jd + i) + 4 * lane) =
+          f32x4{o[jd][4 * i], o[jd][4 * i + 1], o[jd][4 * i + 2], o[jd][4 * i + 3]};
+  p[4096 + lane] = m;
+  p[4160 + lane] = l;
+}
+// (o, m, l) = the state at p merged with the segment in (o, m, l). The blocks
+// are loaded kSegAhead ahead of their merge (fenced: all at once they would not
+// fit the registers).
+constexpr int kSegAhead = 1;
+__device__ __forceinline__ void seg_merge(const float* p, f32x16 (&o)[4], float& m, float& l) {
+  const int lane = threadIdx.x & 63;
+  f32x4 x[kSegAhead + 1][4];
+  auto load = [&](int jd) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      x[jd % (kSegAhead + 1)][i] = *reinterpret_cast<const f32x4*>(p + 256 * (4 * jd + i) + 4 * lane);
+  };
+  const float m0 = p[4096 + lane], l0 = p[4160 + lane];
+#pragma unroll
+  for (int jd = 0; jd < kSegAhead; ++jd) load(jd);
+  const SegWeights w = seg_weights(m0, m, sum_l32(l));
+  l = seg_mix(l0, l, w);
+  m = w.m;
+#pragma unroll
+  for (int jd = 0; jd < 4; ++jd) {
+    if (jd + kSegAhead < 4) load(jd + kSegAhead);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[jd][e] = seg_mix(x[jd % (kSegAhead + 1)][e >> 2][e & 3], o[jd][e], w);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+// Ends a segment inside a workgroup's run over all keys (after its last PV
+// MFMAs, before the new segment's scores need registers): its partial joins the
+// running merge at p (the first segment's becomes it), and the state restarts.
+__device__ __forceinline__ void seg_flush(float* p, bool first, f32x16 (&o)[4], float& m, float& l) {
+  // (hidden from the compiler, which would otherwise compute the addresses
+  // before the step loop and keep them in registers)
+  asm volatile("" : "+s"(p));
+  __builtin_amdgcn_sched_barrier(0);
+  if (!first) seg_merge(p, o, m, l);
+  seg_store(p, o, m, l);
+  __builtin_amdgcn_sched_barrier(0);
+  m = kNoKey;
+  l = 0.f;
+#pragma unroll
+  for (int jd = 0; jd < 4; ++jd)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[jd][e] = 0.f;
+}
+
 // The same attention with a ping-pong schedule for eight waves (two per SIMD).
 // Waves 0-3 and 4-7 form two groups that each hold one wave of every SIMD. A
 // step is split into an MFMA phase (S^T of this step, then O^T += V^T P^T of
@@ -260,6 +355,11 @@ __device__ __forceinline__ void tile_attend(const PagedKV& kv, float scale, cons
 // stages its rows and meets every barrier but issues no MFMA and no softmax
 // work (the two instances keep the same barrier sequence).
 //
+// t_lo is 0 or the start of a segment. With kSeg, a run that passes segment
+// boundaries leaves the merge of all but its last segment at `stash` (this
+// wave's); the step after a boundary is an instance of its own, so the step
+// loop carries nothing of it.
+//
 // kUniformPages: in-page byte offsets fit 31 bits. A wave stages four
 // consecutive key rows of each 32-row set of a step, and pages hold at least
 // eight keys, so each set's page id is the same for the whole wave (kSetPages,
@@ -271,10 +371,10 @@ __device__ __forceinline__ void tile_attend(const PagedKV& kv, float scale, cons
 // sequence's final step, which stays in the page of its set. Otherwise every
 // thread looks up the page of each row it stages.
 template <int kWaves, bool kUniformPages, bool kFp8 = false, bool kCompute = true, bool kSetPages = false,
-          bool kNt = false>
+          bool kNt = false, bool kSeg = false>
 __device__ __forceinline__ void tile_attend_pp(const PagedKV& kv, float scale, const int* bt_row, int g, int t_lo,
                                                int t_hi, int t_full, int limit, const bf16x8 (&qv)[8], TileLds& lds,
-                                               f32x16 (&o)[4], float& m_run, float& l_run, int& bad) {
+                                               f32x16 (&o)[4], float& m_run, float& l_run, int& bad, float* stash) {
   static_assert(kWaves == 8, "the ping-pong schedule pairs two waves on each SIMD");
   constexpr int kAhead = 3;                       // LDS operand reads in flight ahead of the MFMAs
   const int tid = threadIdx.x;
@@ -548,14 +648,32 @@ __device__ __forceinline__ void tile_attend_pp(const PagedKV& kv, float scale, c
   softmax_phase(t_lo);
   next_page(0);
   __syncthreads();
-  for (int j = 1; j < nsteps; ++j) {
-    mfma_phase(yes, yes, (j - 1) & 1, j & 1);
+  auto rest_of_step = [&](int j) {
     stage(j);
     __syncthreads();
     fetch_next(j);
     softmax_phase(t_lo + j * kKeys);
     next_page(j);
     __syncthreads();
+  };
+  constexpr int kSegSteps = kSegKeys / kKeys;
+  // (a split unit's item starts at its segment and meets no boundary)
+  int j = 1, j_seg = kSeg && t_lo == 0 ? kSegSteps : nsteps;   // the next boundary's step
+  for (;;) {
+    const int j_end = min(nsteps, j_seg);
+    for (; j < j_end; ++j) {
+      mfma_phase(yes, yes, (j - 1) & 1, j & 1);
+      rest_of_step(j);
+    }
+    if (!kSeg || j >= nsteps) break;
+    if constexpr (kSeg) {
+      mfma_phase(yes, no, (j - 1) & 1, 0);
+      if constexpr (kCompute) seg_flush(stash, j == kSegSteps, o, m_run, l_run);
+      mfma_phase(no, yes, 0, j & 1);
+      rest_of_step(j);
+    }
+    ++j;
+    j_seg *= 2;
   }
   mfma_phase(yes, no, (nsteps - 1) & 1, 0);
   if (!late) __syncthreads();
@@ -589,7 +707,7 @@ constexpr int kDlVPitch = 1024 + 64;
 constexpr int kDlKBytes = 32 * kDlKPitch;
 constexpr int kDlVBytes = 32 * kDlVPitch;
 
-// Attention of this lane's query column over keys [0, t_hi) of KV head g, as
+// Attention of this lane's query column over keys [t_lo, t_hi) of KV head g, as
 // tile_attend_pp (same arguments and results) for bf16 pages of at least 64
 // keys whose in-page offsets fit 31 bits. Its rounding differs from the
 // 64-key routines (the running max and the sums advance per 128 keys).
@@ -599,11 +717,11 @@ constexpr int kDlVBytes = 32 * kDlVPitch;
 // phase j, by the second group at the start of its softmax phase j-1. Each
 // wave waits for its own loads before the barrier after which they are first
 // read, one MFMA phase and one softmax phase later.
-template <bool kCompute, bool kNt>
-__device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, const int* bt_row, int g, int t_hi,
-                                               int t_full, int limit, const bf16x8 (&qv)[8], char* kl0, char* kl1,
-                                               char* vl0, char* vl1, f32x16 (&o)[4], float& m_run, float& l_run,
-                                               int& bad) {
+template <bool kCompute, bool kNt, bool kSeg>
+__device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, const int* bt_row, int g, int t_lo,
+                                               int t_hi, int t_full, int limit, const bf16x8 (&qv)[8], char* kl0,
+                                               char* kl1, char* vl0, char* vl1, f32x16 (&o)[4], float& m_run,
+                                               float& l_run, int& bad, float* stash) {
   constexpr int kAhead = 3;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -611,8 +729,9 @@ __device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, c
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool late = wave >= 4;
   const float sl2 = scale * kLog2e;
-  if (t_hi <= 0) return;
-  const int nsteps = (t_hi + kDlKeys - 1) / kDlKeys;
+  if (t_lo >= t_hi) return;
+  const int nsteps = (t_hi - t_lo + kDlKeys - 1) / kDlKeys;
+  constexpr int kSegSteps = kSegKeys / kDlKeys;
   const int pmask = kv.page_size - 1;
 
   // loads: wave w fills blocks w + 8 i (i = 0..3) of K and of V; block b holds
@@ -629,7 +748,7 @@ __device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, c
   // page ids of the two halves of step j (scalar loads; a half past the last
   // key takes the first half's page)
   auto page_pair = [&](int j, int (&p)[2]) {
-    const int t0 = j * kDlKeys;
+    const int t0 = t_lo + j * kDlKeys;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int t = (t0 + 64 * h < t_hi) ? t0 + 64 * h : t0;
@@ -645,7 +764,7 @@ __device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, c
   // load that key again
   auto dma_block = [&](int j, const int (&p)[2], const char* base, int64_t sp, uint32_t ss, char* dst, int pitch,
                        int i) {
-    const int t0 = j * kDlKeys;
+    const int t0 = t_lo + j * kDlKeys;
     const int h = i >> 1;
     const int hh = (t0 + 64 * h < t_hi) ? h : 0;      // the half whose page this block reads
     const int last = min(63, t_hi - 1 - t0 - 64 * hh);
@@ -841,37 +960,52 @@ __device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, c
       barrier();
     }
     // step j: K(j) in buffer j % 2, V(j-1) in buffer (j-1) % 2
-    auto body = [&](int j, auto par, auto first) {
-      constexpr int P = decltype(par)::value;
+    constexpr int kFirst = 0, kNext = 1, kFlush = 2;   // kFlush: the step after a segment boundary
+    auto body = [&](int j, auto par, auto kind) {
+      constexpr int P = decltype(par)::value, K = decltype(kind)::value;
       char* kcur = P ? kl1 : kl0;
       char* vprev = P ? vl0 : vl1;
       auto hook = [&](int ii) {
         if constexpr (!kLate) issue_block(j, par, ii);
       };
-      if constexpr (decltype(first)::value)
+      if constexpr (K == kFirst) {
         mfma_phase(no, yes, vprev, kcur, hook);
-      else
+      } else if constexpr (K == kNext) {
         mfma_phase(yes, yes, vprev, kcur, hook);
+      } else {
+        mfma_phase(yes, no, vprev, kcur, hook);
+        if constexpr (kCompute) seg_flush(stash, j == kSegSteps, o, m_run, l_run);
+        mfma_phase(no, yes, vprev, kcur, none);
+      }
       if constexpr (!kLate) issue_done(j);
       if constexpr (kLate) wait_loads();
       barrier();
       if constexpr (kLate) {
         if (j + 1 < nsteps) issue(j + 1, std::integral_constant<int, 1 - P>{});
       }
-      softmax_phase(j * kDlKeys);
+      softmax_phase(t_lo + j * kDlKeys);
       next_pages();
       if constexpr (!kLate) wait_loads();
       barrier();
     };
     const std::integral_constant<int, 0> even{};
     const std::integral_constant<int, 1> odd{};
-    body(0, even, yes);
-    int j = 1;
-    for (; j + 1 < nsteps; j += 2) {
-      body(j, odd, no);
-      body(j + 1, even, no);
+    const std::integral_constant<int, kNext> next{};
+    body(0, even, std::integral_constant<int, kFirst>{});
+    // (a boundary's step is even: a segment is an even number of steps)
+    int j = 1, j_seg = kSeg && t_lo == 0 ? kSegSteps : nsteps;   // the next boundary's step
+    for (;;) {
+      const int j_end = min(nsteps, j_seg);
+      for (; j + 1 < j_end; j += 2) {
+        body(j, odd, next);
+        body(j + 1, even, next);
+      }
+      if (j < j_end) body(j++, odd, next);
+      if (!kSeg || j >= nsteps) break;
+      if constexpr (kSeg) body(j, even, std::integral_constant<int, kFlush>{});
+      ++j;
+      j_seg *= 2;
     }
-    if (j < nsteps) body(j, odd, no);
     // PV of the final step: V(n-1) in buffer (n-1) % 2
     if ((nsteps - 1) & 1)
       mfma_phase(yes, no, vl1, kl0, none);
@@ -888,18 +1022,21 @@ __device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, c
 // Normalised output row of this lane's column: element (jd, q, i) of o holds
 // dimension 32 jd + 8 q + 4 (lane/32) + i.
 template <typename T>
-__device__ __forceinline__ void store_o_row(T* row, const f32x16 (&o)[4], float inv) {
+__device__ __forceinline__ void store_o_block(T* row, const f32x16& o, int jd, float inv) {
   const int kg = (threadIdx.x & 63) >> 5;
   typedef T t4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-  for (int jd = 0; jd < 4; ++jd)
+  for (int q = 0; q < 4; ++q) {
+    t4 w;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      t4 w;
+    for (int i = 0; i < 4; ++i) w[i] = (T)(o[4 * q + i] * inv);
+    *reinterpret_cast<t4*>(row + 32 * jd + 8 * q + 4 * kg) = w;
+  }
+}
+template <typename T>
+__device__ __forceinline__ void store_o_row(T* row, const f32x16 (&o)[4], float inv) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) w[i] = (T)(o[jd][4 * q + i] * inv);
-      *reinterpret_cast<t4*>(row + 32 * jd + 8 * q + 4 * kg) = w;
-    }
+  for (int jd = 0; jd < 4; ++jd) store_o_block(row, o[jd], jd, inv);
 }
 
 }  // namespace rl

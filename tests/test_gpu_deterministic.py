@@ -159,6 +159,65 @@ def test_extend_prefill_equals_token_by_token(ps):
     H.compare(out, ref_o, lse, ref_l, what="prefill")
 
 
+SEGMENT_CASES = [
+    # (page_size, Hq, Hkv, fp8)
+    (64, 16, 8, False),      # 128-key steps
+    (128, 24, 2, True),      # 64-key steps, one page id per step
+    (16, 12, 3, False),      # 64-key steps, a page id per row set; heads do not divide by the XCDs
+]
+
+
+@pytest.mark.parametrize("case", SEGMENT_CASES, ids=[f"P{c[0]}_h{c[1]}kv{c[2]}_{'fp8' if c[3] else 'bf16'}" for c in SEGMENT_CASES])
+def test_split_and_whole_units_give_the_same_bits(case):
+    """Rows around the key-segment boundaries: in a small call the planner splits their
+    keys between workgroups, in one of many rows each unit is whole. The lengths
+    are views of one sequence's pages."""
+    ps, hq, hkv, fp8 = case
+    w = wl.custom(140 + ps, "decode", [33000], hq=hq, hkv=hkv, page_size=ps)
+    H.say(f"split against whole units {case}")
+    t = (wl.materialize_fp8 if fp8 else wl.materialize)(w, DEV)
+    edges = [1, 64, 4097, 16383, 16384, 16385, 16386, 16448, 16512, 32767, 32768, 32769, 33000]
+    n = max(len(edges), 4000 // hkv)              # more than four units per CU: no unit is split
+    lens = (edges * -(-n // len(edges)))[:n]
+    g = torch.Generator(device=DEV)
+    g.manual_seed(7)
+    many = dict(t, q=torch.randn((n, hq, 128), generator=g, device=DEV).to(torch.bfloat16),
+                block_table=t["block_table"].expand(n, -1).contiguous(),
+                kv_lens=torch.tensor(lens, dtype=torch.int32, device=DEV))
+    full_o, full_l = det_decode(many, fp8=fp8)
+    for rows in ([len(edges) - 1], [4, 5, 6], list(range(len(edges)))):
+        o, l = det_decode(many, rows=rows, fp8=fp8)
+        idx = torch.tensor(rows, device=DEV)
+        assert bits_equal(o, full_o[idx]), f"rows {rows}: split keys change the bits"
+        assert bits_equal(l, full_l[idx]), f"rows {rows}: split keys change the lse"
+    sel = list(range(len(edges)))
+    call = ra.decode_fp8 if fp8 else ra.decode
+    args = (many["k_pages"], many["v_pages"]) + ((t["k_scale"], t["v_scale"]) if fp8 else ())
+    lse = torch.empty((len(sel), hq), dtype=torch.float32, device=DEV)
+    ref = call(many["q"][sel].contiguous(), *args, many["block_table"][sel].contiguous(),
+               many["kv_lens"][sel].contiguous(), t["scale"], lse=lse)
+    H.compare(full_o[sel], H.f64(ref), max_abs=2e-2, rel_rms=5e-3, what="segments vs split-KV decode")
+
+
+@pytest.mark.parametrize("ps", [16, 64])
+def test_chunk_across_a_segment_boundary(ps):
+    """A chunk whose tokens lie on both sides of a boundary: rows before it see no key of the
+    later segment; against the oracle, and token by token bitwise."""
+    n, kv = 150, 16384 + 90
+    w = wl.custom(150 + ps, "extend", [kv, 32768 + 3], q_lens=[n, 40], hq=16, hkv=2, page_size=ps)
+    H.say(f"chunk across a segment boundary P={ps}")
+    t = wl.materialize(w, DEV)
+    out, lse = H.run_extend(w, t)
+    ref_o, ref_l = H.oracle_full(w, t)
+    H.compare(out, ref_o, lse, ref_l, what="chunk across a boundary")
+    rows = torch.arange(n, device=DEV)
+    step = {"q": t["q"][rows].contiguous(), "k_pages": t["k_pages"], "v_pages": t["v_pages"],
+            "block_table": t["block_table"][0:1].expand(n, -1).contiguous(),
+            "kv_lens": torch.arange(kv - n + 1, kv + 1, dtype=torch.int32, device=DEV), "scale": t["scale"]}
+    dec_o, dec_l = det_decode(step)
+    assert bits_equal(dec_o, out[rows]) and bits_equal(dec_l, lse[rows])
+
+
 def test_deterministic_decode_full_size_sampled():
     """The ragged 64K batch in deterministic mode: sampled sequences vs the oracle."""
     w = wl.decode_ragged()

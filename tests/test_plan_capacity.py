@@ -237,6 +237,73 @@ def test_extend_capacity_covers_planner(seed):
         assert units <= caps["max_items"]
 
 
+SEGMENT = 16384     # keys of an extend row's first segment; the later ones double
+
+
+def segment_start(s):
+    return SEGMENT << (s - 1) if s > 0 else 0
+
+
+def segment_count(n):
+    return 1 if n <= SEGMENT else 1 + ((n - 1) // SEGMENT).bit_length()
+
+
+def segment_tiles(s, prefix, n, nt, tt):
+    """Tiles whose keys reach into segment s, as the extend planner counts them."""
+    t = segment_start(s)
+    if t >= prefix + n:
+        return 0
+    return nt if t <= prefix else nt - (t - prefix) // tt
+
+
+@pytest.mark.parametrize("seed", range(30))
+def test_split_units_cover_every_segment_once(seed):
+    """The planner's item order (segment by segment from the last, last tile first) against
+    the units' key ranges, and the merge's walk over a unit's slots against that order."""
+    rng = np.random.default_rng(seed)
+    tt = int(rng.choice([1, 2, 21, 32, 256]))
+    n = int(rng.integers(1, int(rng.choice([2, 300, 36000]))))
+    prefix = int(rng.choice([0, 1, SEGMENT - n % SEGMENT, SEGMENT, int(rng.integers(0, 160000))]))
+    nt = ceil_div(n, tt)
+    first_row = [(nt - 1 - j) * tt for j in range(nt)]                    # tile j of the emission order
+    keys = [prefix + r + min(tt, n - r) for r in first_row]
+    want = {(s, j) for j in range(nt) for s in range(64) if segment_start(s) < keys[j]}
+    assert all(segment_count(k) == sum(segment_start(s) < k for s in range(64)) for k in keys)
+    n_seg = segment_count(prefix + n)
+    per = sum(segment_tiles(s, prefix, n, nt, tt) for s in range(n_seg))
+    assert per == len(want)
+    items = []
+    for u in range(per):
+        j, seg = u, n_seg - 1
+        c = segment_tiles(seg, prefix, n, nt, tt)
+        while j >= c:
+            j -= c
+            seg -= 1
+            c = segment_tiles(seg, prefix, n, nt, tt)
+        items.append((seg, j))
+    assert set(items) == want and len(set(items)) == per
+    for j in range(nt):
+        slot = per - nt + j
+        for s in range(segment_count(keys[j])):
+            assert items[slot] == (s, j)
+            slot -= segment_tiles(s + 1, prefix, n, nt, tt)
+
+
+def test_extend_workspace_has_room_for_splits():
+    """The size query covers the list, the slots of split units and a running merge per
+    workgroup as soon as the block table holds more than a segment, and nothing of
+    them below that."""
+    small = ra.extend_workspace_size(4, 100, 64, 8, SEGMENT // 64, 64)
+    large = ra.extend_workspace_size(4, 100, 64, 8, SEGMENT // 64 + 1, 64)
+    units = ra.diag_extend_capacity(4, 100, 64, 8)["max_items"]
+    wave = 64 * 66 * 4
+    assert small == 256 + align256(units * 16)
+    # two segments per unit, 8 waves per slot, and a merge state for each CU
+    assert large >= small + (2 * units + min(units, 256)) * 8 * wave
+    # the slots are bounded whatever the sizes
+    assert ra.extend_workspace_size(1000, 100000, 64, 8, 16384, 64) < 2 ** 30
+
+
 def test_capacity_model_reaches_its_bounds():
     """The model is not vacuous: a forced small split on a long batch uses most of the
     slot capacity, and trajectory groups produce shared items."""
