@@ -22,74 +22,15 @@
 // sequences of 1-32K keys (192 units): 604 -> 351 us.
 #include <algorithm>
 #include <type_traits>
+#include <vector>
 
+#include "extend_plan.hpp"
 #include "kernels.hpp"
 #include "tile_attn.hpp"
 
 namespace rl {
 
 namespace {
-
-constexpr int kSortMax = 1024;          // sequences sorted by key count up to this batch size
-constexpr int kXcds = 8;                // workgroups go to the 8 XCDs round-robin by index
-constexpr bool kXcdGroups = true;       // keep each (sequence, KV head)'s units on one XCD
-
-struct SeqRange {
-  int q0, n, kv;
-};
-
-__device__ __forceinline__ SeqRange seq_range(const ExtendArgs& a, int b, int* bad) {
-  const int max_tokens = a.kv.max_pages * a.kv.page_size;
-  if (a.decode_rows) {
-    // decode: sequence b owns rows b * n .. b * n + n - 1, its last n keys
-    const int n = a.decode_rows;
-    int kv = a.kv_lens[(int64_t)b * a.kv_lens_s];
-    if (kv < 0 || kv > max_tokens) {
-      *bad |= kErrLen;
-      kv = kv < 0 ? 0 : max_tokens;
-    }
-    if (kv == 0) return {b * n, 0, 0};
-    if (kv < n) {
-      *bad |= kErrKvShort;
-      kv = n <= max_tokens ? n : max_tokens;
-    }
-    return {b * n, n, kv};
-  }
-  int q0 = a.qo_indptr[(int64_t)b * a.indptr_s];
-  int q1 = a.qo_indptr[(int64_t)(b + 1) * a.indptr_s];
-  if (q0 < 0 || q0 > a.total_q || q1 < q0 || q1 > a.total_q) {
-    *bad |= kErrIndptr;
-    q0 = q0 < 0 ? 0 : (q0 > a.total_q ? a.total_q : q0);
-    q1 = q1 < q0 ? q0 : (q1 > a.total_q ? a.total_q : q1);
-  }
-  int n = q1 - q0;
-  int kv = a.kv_lens[(int64_t)b * a.kv_lens_s];
-  if (kv < 0 || kv > max_tokens) {
-    *bad |= kErrLen;
-    kv = kv < 0 ? 0 : max_tokens;
-  }
-  if (n > kv) {           // the chunk must be inside the cache
-    *bad |= kErrKvShort;
-    if (n > max_tokens) n = max_tokens;
-    kv = n;
-  }
-  return {q0, n, kv};
-}
-
-// Tiles of tt chunk rows (nt in all; chunk of n rows behind `prefix` keys)
-// whose keys reach into segment s: all but the first tiles, which end before it.
-__device__ __forceinline__ int segment_tiles(int s, int prefix, int n, int nt, int tt) {
-  const int t = segment_start(s);
-  if (t >= prefix + n) return 0;
-  return t <= prefix ? nt : nt - (t - prefix) / tt;
-}
-// (tile, segment) pairs of one head group of a sequence
-__device__ __forceinline__ long long unit_segments(const SeqRange& r, int tt) {
-  const int nt = (r.n + tt - 1) / tt;
-  long long c = 0;
-  for (int s = segment_count(r.kv) - 1; s >= 0; --s) c += segment_tiles(s, r.kv - r.n, r.n, nt, tt);
-  return c;
-}
 
 __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
   __shared__ int order[kSortMax];
@@ -99,7 +40,7 @@ __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
   // head group, first split unit)
   __shared__ int4 seq_a[1024];
   __shared__ int4 seq_b[1024];
-  __shared__ unsigned long long all_keys;
+  __shared__ unsigned long long all_keys, all_units;
   __shared__ int wave_tot[16];
   const int tid = threadIdx.x;
   int bad = 0;
@@ -141,26 +82,22 @@ __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
   }
   const bool sorted = a.B <= kSortMax;
   const int heads = a.Hkv * a.head_blocks, tt = a.tile_tokens;
-  auto tiles = [&](int n) { return (n + tt - 1) / tt; };
+  auto tiles = [&](int n) { return unit_tiles(n, tt); };
   if (sorted) {
-    // Which sequences are split: those with a unit longer than half a
-    // workgroup's share of the call's keys, as far as the slots go. Below
-    // that, whole units in longest-first order fill the chip: six sequences of
-    // 15-24K keys, 57K a workgroup, took 1.735 ms whole and 1.771 ms split;
-    // one of 23.8K, 8.2K a workgroup, 527 and 314 us (segments from 4096).
     const bool may_split = a.max_slots > 0;
     SeqRange r{0, 0, 0};
     if (tid < a.B) r = seq_range(a, tid, &bad);
     int need = 0;
     if (may_split) {
-      if (tid == 0) all_keys = 0;
+      if (tid == 0) all_keys = all_units = 0;
       __syncthreads();
-      if (r.n > 0) atomicAdd(&all_keys, (unsigned long long)tiles(r.n) * (unsigned long long)heads * r.kv);
-      __syncthreads();
-      if (r.kv > kSegKeys && r.n > 0 && (unsigned long long)r.kv * (2 * a.workers) > all_keys) {
-        const long long n = (long long)heads * unit_segments(r, tt);
-        need = n > a.max_slots ? a.max_slots + 1 : (int)n;
+      if (r.n > 0) {
+        const unsigned long long units = (unsigned long long)tiles(r.n) * (unsigned long long)heads;
+        atomicAdd(&all_units, units);
+        atomicAdd(&all_keys, units * r.kv);
       }
+      __syncthreads();
+      need = split_need(a, r, all_keys, all_units);
     }
     int tot, first = 0;
     if (may_split) first = block_exclusive_scan(need, &tot, wave_tot);
@@ -178,10 +115,6 @@ __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
     }
     __syncthreads();
   }
-  // With a multiple of 8 head groups, group gh of a sequence runs on XCD
-  // gh % 8: its units share their keys through that XCD's L2 instead of
-  // every XCD streaming every group's keys. Each XCD's units stay in list
-  // order (longest first), and every XCD gets the same number of units.
   const bool xcd = kXcdGroups && heads % kXcds == 0;
   int offset = 0, moffset = 0;
   for (int p0 = 0; p0 < a.B; p0 += blockDim.x) {
@@ -208,37 +141,8 @@ __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
     const int lps = 1 << lps_log, s = tid >> lps_log;
     if (s < n_seq) {
       const int4 sa = seq_a[s], sb = seq_b[s];
-      const int nt = tiles(sa.y);
-      for (int i = tid & (lps - 1); i < sb.y * heads; i += lps) {
-        const int gh = i / sb.y, u = i - gh * sb.y;
-        const int g = gh / a.head_blocks, hb = gh - g * a.head_blocks;
-        // last tile first: it has the longest key range of the sequence; a
-        // split sequence's items go segment by segment, so that the tiles
-        // that read the same keys are neighbours, the last (longest) first
-        int j = u, seg = -1;
-        if (sa.w >= 0) {
-          seg = segment_count(sa.z + sa.y) - 1;
-          for (int c = segment_tiles(seg, sa.z, sa.y, nt, tt); j >= c; c = segment_tiles(seg, sa.z, sa.y, nt, tt)) {
-            j -= c;
-            --seg;
-          }
-        }
-        int idx = sb.x + i;
-        if (xcd)   // position in the XCD's own list, behind its items of the earlier sequences and groups
-          idx = (sb.x / kXcds + (gh / kXcds) * sb.y + u) * kXcds + gh % kXcds;
-        const int i0 = (nt - 1 - j) * tt;
-        const int4 unit = make_int4(sa.x, i0, min(tt, sa.y - i0), g | (hb << 16));
-        if (idx >= a.max_items) {
-          bad |= kErrCapacity;     // the host sizing rules this out; reported, never dropped silently
-          continue;
-        }
-        a.ws.items[idx] = unit;
-        if (a.ws.segs) a.ws.segs[idx] = make_int2(seg, seg < 0 ? -1 : sa.w + i);
-        if (seg == 0) {              // every tile reaches into segment 0
-          a.ws.munits[sb.z + gh * nt + j] = unit;
-          a.ws.mslots[sb.z + gh * nt + j] = make_int2(sa.w + (gh + 1) * sb.y - nt, j);
-        }
-      }
+      const SeqPlan plan{sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z};
+      for (int i = tid & (lps - 1); i < sb.y * heads; i += lps) bad |= place_item(a, plan, i, xcd);
     }
     offset += tot;
     moffset += mtot;
@@ -451,6 +355,49 @@ __global__ __launch_bounds__(256) void merge_segments_kernel(ExtendArgs a) {
 }
 
 }  // namespace
+
+int plan_extend_on_host(const ExtendArgs& a, int* split_seqs) {
+  const int heads = a.Hkv * a.head_blocks;
+  int bad = 0;
+  std::vector<SeqRange> r(a.B);
+  std::vector<int> order(a.B), keys(a.B), slot_of(a.B, -1);
+  unsigned long long all_keys = 0, all_units = 0;
+  for (int b = 0; b < a.B; ++b) {
+    r[b] = seq_range(a, b, &bad);
+    order[b] = b;
+    keys[b] = r[b].kv;
+    const unsigned long long units = (unsigned long long)unit_tiles(r[b].n, a.tile_tokens) * heads;
+    all_units += units;
+    all_keys += units * r[b].kv;
+  }
+  *split_seqs = 0;
+  if (a.B <= kSortMax) {
+    long long first = 0;
+    for (int b = 0; b < a.B && a.max_slots > 0; ++b) {
+      const int need = split_need(a, r[b], all_keys, all_units);
+      if (need > 0 && first + need <= a.max_slots) {
+        slot_of[b] = (int)first;
+        keys[b] = std::max(kSegKeys, r[b].kv / 2);
+        ++*split_seqs;
+      }
+      first += need;
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return keys[x] > keys[y]; });
+  }
+  int offset = 0, moffset = 0;
+  for (int p = 0; p < a.B; ++p) {
+    const SeqRange& s = r[order[p]];
+    const int slot = slot_of[order[p]];
+    const int per = slot >= 0 ? (int)unit_segments(s, a.tile_tokens) : unit_tiles(s.n, a.tile_tokens);
+    const SeqPlan plan{order[p], s.n, s.kv - s.n, slot, offset, per, moffset};
+    for (int i = 0; i < per * heads; ++i) bad |= place_item(a, plan, i, kXcdGroups && heads % kXcds == 0);
+    offset += per * heads;
+    if (slot >= 0) moffset += unit_tiles(s.n, a.tile_tokens) * heads;
+  }
+  a.ws.hdr[0] = offset < a.max_items ? offset : a.max_items;
+  a.ws.hdr[1] = moffset;
+  return bad;
+}
 
 hipError_t launch_extend(const ExtendArgs& a, hipStream_t stream, KernelTimer* timer) {
   plan_extend_kernel<<<1, 1024, 0, stream>>>(a);

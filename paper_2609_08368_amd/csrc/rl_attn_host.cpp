@@ -16,6 +16,7 @@
 #include <utility>
 #include <vector>
 
+#include "extend_plan.hpp"
 #include "kernels.hpp"
 #include "rl_attn.h"
 #include "rl_attn_diag.h"
@@ -1278,6 +1279,87 @@ int rl_attn_diag_extend_capacity(int64_t batch, int64_t total_q, int64_t num_q_h
   out[1] = sh.rows_head;
   out[2] = sh.tile_tokens;
   out[3] = sh.head_blocks;
+  return RL_OK;
+}
+
+int rl_attn_diag_extend_plan(const int32_t* qo_indptr, const int32_t* kv_lens, int64_t batch, int64_t total_q,
+                             int64_t query_tokens, int64_t num_q_heads, int64_t num_kv_heads, int64_t max_tokens,
+                             int32_t cus, int64_t* out) {
+  if (!kv_lens || !out || (query_tokens == 0 && !qo_indptr))
+    return fail(RL_ERR_INVALID_ARG, "diag_extend_plan: null pointer");
+  if (batch <= 0 || batch > (1 << 22) || total_q < 0 || total_q > INT32_MAX / 2 || query_tokens < 0 ||
+      query_tokens > 64 || num_q_heads <= 0 || num_kv_heads <= 0 || num_q_heads % num_kv_heads != 0 ||
+      num_q_heads > 4096 || max_tokens < 0 || max_tokens > INT32_MAX || cus < 1)
+    return fail(RL_ERR_INVALID_ARG, "diag_extend_plan: invalid sizes");
+  const int64_t R = num_q_heads / num_kv_heads;
+  const ExtendShape sh = extend_shape(R);
+  const ExtendLayout L =
+      extend_layout(batch, total_q, query_tokens ? query_tokens : total_q, num_kv_heads, R, max_tokens, cus);
+  rl::ExtendArgs a{};
+  a.kv.max_pages = (int)max_tokens;      // (a page size of 1: only their product counts)
+  a.kv.page_size = 1;
+  a.qo_indptr = qo_indptr;
+  a.kv_lens = kv_lens;
+  a.indptr_s = a.kv_lens_s = 1;
+  a.B = (int)batch;
+  a.total_q = (int)total_q;
+  a.Hq = (int)num_q_heads;
+  a.Hkv = (int)num_kv_heads;
+  a.R = (int)R;
+  a.decode_rows = (int)query_tokens;
+  a.rows_head = sh.rows_head;
+  a.tile_tokens = sh.tile_tokens;
+  a.head_blocks = sh.head_blocks;
+  a.workers = L.workers;
+  a.max_slots = L.max_slots;
+  a.max_items = L.max_units + L.max_slots;
+  const int4 none = make_int4(-1, -1, -1, -1);
+  int hdr[64] = {};
+  std::vector<int4> items((size_t)a.max_items, none), munits((size_t)L.max_slots, none);
+  std::vector<int2> segs((size_t)a.max_items, make_int2(-1, -1)), mslots((size_t)L.max_slots, make_int2(-1, -1));
+  a.ws.hdr = hdr;
+  a.ws.items = items.data();
+  if (L.max_slots > 0) {
+    a.ws.segs = segs.data();
+    a.ws.munits = munits.data();
+    a.ws.mslots = mslots.data();
+  }
+  int split_seqs = 0;
+  const int bad = rl::plan_extend_on_host(a, &split_seqs);
+  // the units that will be finished, and of them those without all their parts in the list
+  std::vector<char> have((size_t)L.max_slots, 0);
+  int64_t listed = 0, parts = 0, broken = 0;
+  for (size_t i = 0; i < items.size(); ++i)
+    if (items[i].x >= 0) {
+      ++listed;
+      if (segs[i].y < 0) continue;
+      ++parts;
+      have[segs[i].y] = 1;
+    }
+  for (int u = 0; u < hdr[1]; ++u) {
+    const int4 it = munits[u];
+    if (it.x < 0) {
+      ++broken;
+      continue;
+    }
+    int dummy = 0;
+    const rl::SeqRange r = rl::seq_range(a, it.x, &dummy);
+    const int prefix = r.kv - r.n, nt = rl::unit_tiles(r.n, a.tile_tokens);
+    int slot = mslots[u].x + mslots[u].y;
+    bool whole = true;
+    for (int s = 0; s < rl::segment_count(prefix + it.y + it.z); ++s) {
+      whole = whole && slot >= 0 && slot < L.max_slots && have[slot];
+      slot -= rl::segment_tiles(s + 1, prefix, r.n, nt, a.tile_tokens);
+    }
+    broken += !whole;
+  }
+  out[0] = listed;
+  out[1] = parts;
+  out[2] = split_seqs;
+  out[3] = hdr[1];
+  out[4] = broken;
+  out[5] = bad;
+  out[6] = L.max_units;
   return RL_OK;
 }
 

@@ -85,12 +85,14 @@ def lib() -> ctypes.CDLL:
         i64p = ctypes.POINTER(ctypes.c_int64)
         L.rl_attn_diag_decode_capacity.argtypes = [ctypes.c_int64] * 6 + [ctypes.c_int32] * 4 + [i64p]
         L.rl_attn_diag_extend_capacity.argtypes = [ctypes.c_int64] * 4 + [i64p]
+        L.rl_attn_diag_extend_plan.argtypes = [vp, vp] + [ctypes.c_int64] * 6 + [ctypes.c_int32, i64p]
         for name in ("rl_attn_decode", "rl_attn_extend", "rl_attn_decode_ex", "rl_attn_extend_ex",
                      "rl_attn_decode_noalloc",
                      "rl_attn_decode_fp8", "rl_attn_extend_fp8", "rl_attn_append_kv", "rl_attn_append_kv_fp8",
                      "rl_attn_merge", "rl_attn_check_device_errors", "rl_attn_reserve_workspace",
                      "rl_attn_profile_enable", "rl_attn_profile_read", "rl_attn_diag_read_bandwidth",
-                     "rl_attn_diag_mfma_bf16", "rl_attn_diag_decode_capacity", "rl_attn_diag_extend_capacity"):
+                     "rl_attn_diag_mfma_bf16", "rl_attn_diag_decode_capacity", "rl_attn_diag_extend_capacity",
+                     "rl_attn_diag_extend_plan"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
     return _lib
@@ -337,3 +339,19 @@ def diag_extend_capacity(batch, total_q, num_q_heads, num_kv_heads) -> dict:
     out = (ctypes.c_int64 * 4)()
     _check(lib().rl_attn_diag_extend_capacity(batch, total_q, num_q_heads, num_kv_heads, out))
     return dict(zip(("max_items", "rows_head", "tile_tokens", "head_blocks"), (int(x) for x in out)))
+
+
+def diag_extend_plan(kv_lens, num_q_heads, num_kv_heads, max_tokens, qo_indptr=None, total_q=None, query_tokens=0,
+                     cus=256) -> dict:
+    """The work list of an extend call (``qo_indptr`` given) or of a deterministic decode of ``query_tokens`` tokens
+    per sequence, planned on the host from host lengths."""
+    b = len(kv_lens)
+    lens = (ctypes.c_int32 * b)(*[int(x) for x in kv_lens])
+    ind = None if qo_indptr is None else (ctypes.c_int32 * (b + 1))(*[int(x) for x in qo_indptr])
+    if total_q is None:
+        total_q = b * query_tokens if qo_indptr is None else int(qo_indptr[-1])
+    out = (ctypes.c_int64 * 7)()
+    _check(lib().rl_attn_diag_extend_plan(ind, lens, b, total_q, query_tokens, num_q_heads, num_kv_heads, max_tokens,
+                                          cus, out))
+    keys = ("items", "parts", "split_seqs", "split_units", "broken_units", "errors", "max_units")
+    return dict(zip(keys, (int(x) for x in out)))

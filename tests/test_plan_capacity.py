@@ -289,6 +289,66 @@ def test_split_units_cover_every_segment_once(seed):
             slot -= segment_tiles(s + 1, prefix, n, nt, tt)
 
 
+# error bits of a plan
+ERR_INDPTR, ERR_CAPACITY = 4, 32
+
+
+def test_split_units_of_overlapping_chunks_are_not_finished_without_their_parts():
+    """A qo_indptr that runs back makes chunks overlap: more units than total_q allows for, so the
+    list cannot hold them. A unit that is finished from parts must have all of them in the list."""
+    ind = [0, 256] * 7 + [0]
+    plan = ra.diag_extend_plan([20000] * 14, 64, 8, 20480, qo_indptr=ind, total_q=256)
+    assert plan["errors"] & ERR_INDPTR
+    assert plan["broken_units"] == 0, plan
+    # the same lengths with chunks that do not overlap: split, and nothing is missing
+    ind = [0] + [256 * (i // 2 + 1) for i in range(14)]
+    plan = ra.diag_extend_plan([20000] * 14, 64, 8, 20480, qo_indptr=ind)
+    assert plan["errors"] == 0 and plan["split_seqs"] > 0 and plan["broken_units"] == 0, plan
+
+
+@pytest.mark.parametrize("seed", range(150))
+def test_every_plan_is_complete_or_reported(seed):
+    """Drawn batches, valid and not: a valid one is listed whole, without an error; with an invalid
+    qo_indptr or lengths outside the table, what falls off the list is reported, and
+    no split unit is finished without all of its parts."""
+    rng = np.random.default_rng(seed)
+    B = int(rng.choice([1, 2, 14, 40, 300, 1024, 1100]))
+    hkv, R = int(rng.choice([1, 2, 8])), int(rng.choice([1, 8, 12, 96, 300]))
+    room = int(rng.choice([SEGMENT, 20480, 2 * SEGMENT, 65536, 1 << 20]))
+    cus = int(rng.choice([8, 64, 256]))
+    n_max = int(rng.choice([2, 80, 700]))
+    n = rng.integers(0, n_max, size=B)
+    kv = np.minimum(n + rng.integers(0, int(rng.choice([300, 20000, 40000, room])), size=B), room)
+    n = np.minimum(n, kv)
+    kind = ["valid", "indptr", "lengths", "decode"][seed % 4]
+    if kind == "decode":
+        tok = int(rng.choice([1, 4, 64]))
+        plan = ra.diag_extend_plan(kv, hkv * R, hkv, room, query_tokens=tok, cus=cus)
+        assert plan["errors"] & ERR_CAPACITY == 0 and plan["broken_units"] == 0, plan
+        return
+    ind = np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
+    total = int(ind[-1])
+    if kind == "indptr":
+        at = rng.random(B + 1) < rng.choice([0.1, 0.5, 1.0])
+        ind[at] = rng.choice([0, total, total // 2, -5, total + 7, 2 ** 31 - 1], size=int(at.sum()))
+        if rng.random() < 0.5:
+            ind = np.where(np.arange(B + 1) % 2 == 0, 0, total)
+            kv = np.full(B, room - int(rng.integers(0, 500)))
+    elif kind == "lengths":
+        at = rng.random(B) < 0.3
+        kv[at] = rng.choice([-1, 0, room + 1, 2 ** 31 - 1], size=int(at.sum()))
+    plan = ra.diag_extend_plan(kv, hkv * R, hkv, room, qo_indptr=ind, total_q=total, cus=cus)
+    assert plan["broken_units"] == 0, plan
+    if kind == "valid":
+        tt = max(1, 256 // min(R, 256))
+        heads = hkv * ceil_div(R, min(R, 256))
+        units = sum(ceil_div(int(x), tt) for x in n) * heads
+        assert plan["errors"] == 0
+        # whole units, and the parts of the split ones
+        assert plan["items"] - plan["parts"] + plan["split_units"] == units
+        assert (plan["parts"] > plan["split_units"]) == (plan["split_seqs"] > 0)
+
+
 def test_extend_workspace_has_room_for_splits():
     """The size query covers the list, the slots of split units and a running merge per
     workgroup as soon as the block table holds more than a segment, and nothing of
