@@ -180,9 +180,10 @@ int rl_attn_extend_ex(const rl_tensor* q, const rl_tensor* qo_indptr, const rl_t
  * hipMalloc). Arguments, results and options are those of rl_attn_decode_ex
  * (bf16 pages), and it runs the same kernels; its workspace is instead a
  * statically allocated array of 160 MiB per device (its first 256 bytes are an
- * error word), held by every device the library runs on until the process ends.
+ * error word) and 33 MiB for the running merges of a deterministic decode, held
+ * by every device the library runs on until the process ends.
  * The call makes no hipMalloc, hipFree or other allocating call.
- * Limit: a call whose workspace would exceed 160 MiB - 256 B is rejected with
+ * Limit: a call that cannot do with 160 MiB - 256 B is rejected with
  * RL_ERR_WORKSPACE before any launch (the workspace grows with the batch, the
  * query heads and query tokens per sequence, and, with a forced split, with
  * max_pages * page_size / split_tokens; e.g. batch 128 with 96 query heads, one
@@ -276,7 +277,9 @@ const char* rl_attn_last_error(void);
 int rl_attn_check_device_errors(void* stream);
 
 /* Grows this (device, stream)'s workspace to at least `bytes` now, so later
- * calls (e.g. under stream capture) need no allocation. */
+ * calls (e.g. under stream capture) need no allocation. Every workspace is
+ * allocated with 132 KB per compute unit (33 MiB) behind it, for the running
+ * merges of extend units over more than 16384 keys. */
 int rl_attn_reserve_workspace(size_t bytes, void* stream);
 
 /* Workspace bytes a decode / extend call with these sizes may need on the
@@ -284,10 +287,13 @@ int rl_attn_reserve_workspace(size_t bytes, void* stream);
  * Decode: query_tokens query tokens per sequence (1 for a 3-D q, n for q
  * [B, n, Hq, 128]) and split_tokens the opts.split_tokens the call will pass
  * (0 = automatic); the size covers bf16 and FP8 pages, prefix sharing on or off
- * and the deterministic mode. Block tables of more than 16384 tokens per sequence
- * take up to about 300 MB more for extend and deterministic decode (partials
- * of keys split between workgroups, at most 256 MB, and one state per
- * workgroup). Returns 0 for sizes a call would reject. */
+ * and the deterministic mode. Neither size falls when batch, rows, tokens or
+ * max_pages grow, so the largest call's serves the smaller ones. Block tables of
+ * more than 16384 tokens per sequence take up to 256 MiB more, for the partials
+ * of keys split between workgroups (extend, deterministic decode, and the
+ * multi-token decode of FP8 pages or pages below 64 keys): without that room,
+ * under capture or where it cannot be allocated, such a call gives the same
+ * bits with no key split. Returns 0 for sizes a call would reject. */
 size_t rl_attn_decode_workspace_size(int64_t batch, int64_t num_q_heads, int64_t num_kv_heads,
                                      int64_t max_pages, int64_t page_size, int64_t query_tokens,
                                      int32_t split_tokens);

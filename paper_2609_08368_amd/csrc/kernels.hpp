@@ -148,7 +148,7 @@ struct ExtendPlanWs {
   int4* munits;    // [min(max_slots, units)] split units, as items
   int2* mslots;    // (first slot of the unit's head group, the unit's place in its segments)
   float* part;     // [max_slots, slot_waves, kSegWaveFloats] partials of split units
-  float* stash;    // [workgroups, slot_waves, kSegWaveFloats] running merges of unsplit units
+  float* stash;    // [workers, slot_waves, kSegWaveFloats] running merges of unsplit units
   int* err;
 };
 
@@ -248,7 +248,8 @@ constexpr size_t kScratchBytes = size_t(160) << 20;
 constexpr size_t kScratchErrBytes = 256;
 // behind them, the running merges of a deterministic decode: room for 256
 // workgroups of 8 waves
-constexpr size_t kScratchStashBytes = size_t(256) * 8 * kSegWaveFloats * 4;
+constexpr int kScratchStashWgs = 256;
+constexpr size_t kScratchStashBytes = size_t(kScratchStashWgs) * 8 * kSegWaveFloats * 4;
 hipError_t scratch_address(hipStream_t stream, void** ptr);
 bool scratch_address_if_set_up(void** ptr);
 // Measurement aids (see rl_attn_diag.h): a grid-stride read of `bytes` and a

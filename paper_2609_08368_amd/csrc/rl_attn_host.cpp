@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdarg>
+#include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -155,9 +156,15 @@ int check_scale(float scale) {
   } while (0)
 
 // ---------------------------------------------------------------- workspace
+// Behind `size` bytes lies room for the running merges of an extend call that
+// takes whole units of more than one key segment (a state per workgroup;
+// null if that could not be allocated), so a workspace of any size that holds a
+// call's list serves it.
 struct Workspace {
   void* ptr = nullptr;
   size_t size = 0;
+  void* stash = nullptr;
+  size_t refused = SIZE_MAX;   // a size that could not be allocated: not tried again for what is merely wanted
   int* err = nullptr;
   // set once a call on this stream was captured into a graph: the graph keeps
   // the buffer's address, so a later growth retires the buffer (freed by
@@ -182,19 +189,28 @@ int device_cus(int dev) {
   return n;
 }
 
-int acquire_ws(hipStream_t st, size_t need, Workspace** out) {
+// running merges of one workgroup per compute unit (units of eight waves)
+size_t stash_bytes(int cus) { return (size_t)cus * 8 * rl::kSegWaveFloats * 4; }
+
+// This (device, stream)'s workspace, with at least `need` bytes (and the running
+// merges' room if `need_stash`). A workspace that is smaller grows to `want`
+// bytes where that can be allocated.
+int acquire_ws(hipStream_t st, size_t need, size_t want, bool need_stash, Workspace** out) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+  const size_t stash = stash_bytes(device_cus(dev));
   std::lock_guard<std::mutex> lk(g_mu);
   Workspace& w = g_ws[{dev, st}];
   const bool need_err = w.err == nullptr;
-  const bool grow = w.size < need;
+  const bool lacks = w.size < need || (need_stash && !w.stash);
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   e = hipStreamIsCapturing(st, &cs);
   if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
   const bool capturing = cs != hipStreamCaptureStatusNone;
-  if (need_err || grow) {
+  const bool may_grow = !capturing && !env().fail_alloc;
+  const bool grow = lacks || (w.size < want && may_grow && want < w.refused);
+  if (need_err || lacks) {
     if (capturing)
       return fail(RL_ERR_WORKSPACE,
                   "workspace must grow to %zu bytes while the stream is being captured; call "
@@ -218,14 +234,25 @@ int acquire_ws(hipStream_t st, size_t need, Workspace** out) {
         w.retired.push_back(w.ptr);
       else
         (void)hipFree(w.ptr);
-      w.ptr = nullptr;
+      w.ptr = w.stash = nullptr;
       w.size = 0;
     }
+    // what the call would like, what it needs, and that without the running merges' room
     void* p = nullptr;
-    e = hipMalloc(&p, need);
-    if (e != hipSuccess) return fail(RL_ERR_WORKSPACE, "hipMalloc(%zu) for the workspace failed: %s", need, hipGetErrorString(e));
+    size_t size = want < w.refused ? want : need, off = 0;
+    for (int t = size == need ? 1 : 0;; ++t) {
+      off = t < 2 ? align256(size) : 0;
+      e = hipMalloc(&p, off ? off + stash : size);
+      if (e == hipSuccess) break;
+      (void)hipGetLastError();                 // a failed attempt is not the next call's error
+      if (t == 2 || (t == 1 && need_stash))
+        return fail(RL_ERR_WORKSPACE, "hipMalloc(%zu) for the workspace failed: %s", size, hipGetErrorString(e));
+      if (t == 0) w.refused = size;
+      size = need;
+    }
     w.ptr = p;
-    w.size = need;
+    w.size = size;
+    w.stash = off ? static_cast<char*>(p) + off : nullptr;
   }
   if (capturing) w.captured = true;
   *out = &w;
@@ -237,15 +264,17 @@ int acquire_ws(hipStream_t st, size_t need, Workspace** out) {
 // device's static scratch array (its first bytes are that array's error word).
 struct WsView {
   char* ptr;
+  size_t size;
   int* err;
+  float* stash;        // running merges of `stash_wgs` workgroups of eight waves
+  int stash_wgs;
 };
 
-int get_ws(hipStream_t st, size_t need, bool noalloc, WsView* v) {
+int get_ws(hipStream_t st, size_t need, size_t want, bool need_stash, int cus, bool noalloc, WsView* v) {
   if (!noalloc) {
     Workspace* w = nullptr;
-    RL_TRY(acquire_ws(st, need, &w));
-    v->ptr = static_cast<char*>(w->ptr);
-    v->err = w->err;
+    RL_TRY(acquire_ws(st, need, want, need_stash, &w));
+    *v = {static_cast<char*>(w->ptr), w->size, w->err, static_cast<float*>(w->stash), cus};
     return RL_OK;
   }
   const size_t room = rl::kScratchBytes - rl::kScratchErrBytes;
@@ -257,8 +286,9 @@ int get_ws(hipStream_t st, size_t need, bool noalloc, WsView* v) {
   void* p = nullptr;
   const hipError_t e = rl::scratch_address(st, &p);
   if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
-  v->ptr = static_cast<char*>(p) + rl::kScratchErrBytes;
-  v->err = static_cast<int*>(p);
+  char* base = static_cast<char*>(p);
+  *v = {base + rl::kScratchErrBytes, room, static_cast<int*>(p), reinterpret_cast<float*>(base + rl::kScratchBytes),
+        rl::kScratchStashWgs};
   return RL_OK;
 }
 
@@ -524,18 +554,24 @@ ExtendShape extend_shape(int64_t R) {
 
 // Workspace of an extend call. Work units are (sequence, KV head, head block,
 // chunk tile): at most Hkv * head_blocks * (B + ceil(total_q / tile_tokens)).
-// Workers (one workgroup per CU) take the units from the list. Where the block
-// table has room for more than one segment of keys (and `segments` allows it),
-// each has a running merge of its own, and units may be split at the segments: every (unit,
-// segment) of a split unit has a slot, at most kMaxSlots of them and kSlotBytes
-// in all (a call with more work than that fills the chip with whole units).
+// Where the block table has room for more than one segment of keys (and
+// `segments` allows it), a workgroup per CU takes them from the list, each with
+// a running merge of its own (kept behind the workspace), and units may be
+// split at the segments: every (unit, segment) of a split unit has a slot.
+// Fewer than 2 `workers` units are split (each is longer than half a worker's
+// share of the keys), so that bounds the slots, besides kMaxSlots and kSlotBytes
+// (a call with more work than that fills the chip with whole units). A
+// workspace that holds the list alone (`list`) is enough: no unit is split then.
+// Both sizes never fall when a size of the call grows, so a workspace for the
+// largest call serves the smaller ones.
 // row_tokens: the most chunk tokens a unit can hold.
 constexpr int64_t kMaxSlots = 4096;
 constexpr int64_t kSlotBytes = int64_t(256) << 20;
 struct ExtendLayout {
   int max_units, max_slots, slot_waves, workers;
   bool segmented;
-  size_t off_munits, off_mslots, off_segs, off_part, off_stash, total;
+  size_t off_munits, off_mslots, off_segs, off_part, list, total;
+  size_t want() const { return max_slots > 0 ? total : list; }
 };
 
 ExtendLayout extend_layout(int64_t B, int64_t total_q, int64_t row_tokens, int64_t Hkv, int64_t R,
@@ -545,34 +581,30 @@ ExtendLayout extend_layout(int64_t B, int64_t total_q, int64_t row_tokens, int64
   const int64_t units = Hkv * s.head_blocks * (B + (total_q + s.tile_tokens - 1) / s.tile_tokens);
   L.max_units = (int)std::min<int64_t>(units, INT32_MAX / 2);
   L.slot_waves = (int)((std::max<int64_t>(1, std::min<int64_t>(row_tokens, s.tile_tokens)) * s.rows_head + 31) / 32);
-  size_t off = 256 + align256((size_t)L.max_units * 16);
+  L.list = 256 + align256((size_t)L.max_units * 16);
   L.workers = (int)std::min<int64_t>(cus, L.max_units);
   L.segmented = segments && max_tokens > rl::kSegKeys;
+  L.total = L.list;
   if (L.segmented) {
     const int64_t slot_bytes = (int64_t)L.slot_waves * rl::kSegWaveFloats * 4;
     const int64_t segs = rl::segment_count((int)std::min<int64_t>(max_tokens, INT32_MAX));
-    if (B <= rl::kSplitBatchMax)
-      L.max_slots = (int)std::min<int64_t>({kMaxSlots, kSlotBytes / slot_bytes, units * segs});
-    L.workers = (int)std::min<int64_t>(cus, (int64_t)L.max_units + L.max_slots);
-    off = 256 + align256((size_t)(L.max_units + L.max_slots) * 16);
+    L.workers = (int)std::min<int64_t>(cus, (int64_t)L.max_units * (1 + segs));
+    const int64_t slots = std::min<int64_t>(kMaxSlots, std::min<int64_t>(L.max_units, 2 * L.workers - 1) * segs);
+    const int64_t part_bytes = std::min<int64_t>(kSlotBytes, slots * slot_bytes);
+    if (B <= rl::kSplitBatchMax) L.max_slots = (int)(part_bytes / slot_bytes);
+    size_t off = 256 + align256((size_t)(L.max_units + slots) * 16);
     L.off_munits = off;
-    off += align256((size_t)L.max_slots * 16);
+    off += align256((size_t)slots * 16);
     L.off_mslots = off;
-    off += align256((size_t)L.max_slots * 8);
+    off += align256((size_t)slots * 8);
     L.off_segs = off;
-    off += align256((size_t)(L.max_units + L.max_slots) * 8);
+    off += align256((size_t)(L.max_units + slots) * 8);
     L.off_part = off;
-    off += align256((size_t)L.max_slots * slot_bytes);
-    L.off_stash = off;
-    off += align256((size_t)L.workers * slot_bytes);
+    off += align256((size_t)part_bytes);
+    L.total = off;
   }
-  L.total = off;
   return L;
 }
-
-// The list alone: what the call cannot do without when its workspace is the
-// static scratch array (the running merges lie behind that array).
-size_t extend_list_bytes(const ExtendLayout& L) { return 256 + align256((size_t)L.max_units * 16); }
 
 int current_cus(int* cus) {
   int dev = 0;
@@ -584,21 +616,17 @@ int current_cus(int* cus) {
 
 // Work-unit shape, workspace and launch of an extend call whose arguments
 // (pages, q, lengths, output) are already filled in. prof_kind: which timing
-// slot the attention kernel is counted under; `given`: a workspace of `L`'s
-// size already carved out of the call's (else the stream's is taken); `room`:
-// bytes of the static scratch array it may use (allocation-free calls; units
-// are split only if all of L fits); `timed`: whether the kernel timer is
-// recorded around the launch.
-int run_extend(rl::ExtendArgs& a, const ExtendLayout& L, hipStream_t st, int prof_kind, bool noalloc = false,
-               const WsView* given = nullptr, size_t room = rl::kScratchBytes - rl::kScratchErrBytes,
-               bool timed = true) {
-  const size_t off_stash = L.segmented ? L.off_stash : L.total;
-  const bool splits = L.max_slots > 0 && (!noalloc || off_stash <= room);
+// slot the attention kernel is counted under; `given`: a workspace of at least
+// L.list bytes already carved out of the call's (else the stream's is taken);
+// `timed`: whether the kernel timer is recorded around the launch.
+int run_extend(rl::ExtendArgs& a, const ExtendLayout& L, int cus, hipStream_t st, int prof_kind, bool noalloc = false,
+               const WsView* given = nullptr, bool timed = true) {
   WsView w{};
   if (given)
     w = *given;
   else
-    RL_TRY(get_ws(st, noalloc ? extend_list_bytes(L) : L.total, noalloc, &w));
+    RL_TRY(get_ws(st, L.list, L.want(), L.segmented, cus, noalloc, &w));
+  const bool splits = L.max_slots > 0 && L.total <= w.size;
   char* base = w.ptr;
   const ExtendShape s = extend_shape(a.R);
   a.rows_head = s.rows_head;
@@ -618,13 +646,8 @@ int run_extend(rl::ExtendArgs& a, const ExtendLayout& L, hipStream_t st, int pro
   }
   a.segmented = L.segmented ? 1 : 0;
   if (L.segmented) {
-    a.ws.stash = reinterpret_cast<float*>(base + L.off_stash);
-    if (noalloc) {
-      // the scratch array's own region (w.err is the array's first word)
-      a.ws.stash = reinterpret_cast<float*>(reinterpret_cast<char*>(w.err) + rl::kScratchBytes);
-      const size_t fit = rl::kScratchStashBytes / ((size_t)L.slot_waves * rl::kSegWaveFloats * 4);
-      a.workers = (int)std::min<size_t>(a.workers, fit);
-    }
+    a.ws.stash = w.stash;
+    a.workers = std::min(a.workers, w.stash_wgs);
   }
   a.ws.err = w.err;
   rl::KernelTimer slot;
@@ -733,7 +756,7 @@ int decode_impl(const rl_tensor* q, const rl_tensor* k_pages, const rl_tensor* v
     // extend's bitwise
     rl::ExtendArgs x = extend_rows();
     x.staged = o.deterministic ? 0 : 1;
-    return run_extend(x, ext, st, 0, noalloc);
+    return run_extend(x, ext, cus, st, 0, noalloc);
   }
   const DecodeLayout lay = decode_layout(B, Hq, Hkv, a.kv.max_pages, a.kv.page_size, o.split_tokens, cus,
                                          o.prefix_share == RL_PREFIX_AUTO, kv_dtype == RL_FP8_E4M3, (int)n_tok);
@@ -743,17 +766,17 @@ int decode_impl(const rl_tensor* q, const rl_tensor* k_pages, const rl_tensor* v
   bool route = n_tok > 1 && o.prefix_share == RL_PREFIX_AUTO && o.split_tokens == 0 && rows_merge &&
                kv_dtype != RL_FP8_E4M3;
   const size_t ext_off = align256(lay.total);
-  const size_t room = rl::kScratchBytes - rl::kScratchErrBytes;
-  size_t need = lay.total;
+  size_t need = lay.total, want = need;
   if (route) {
-    need = ext_off + (noalloc ? extend_list_bytes(ext) : ext.total);
-    if (noalloc && need > room) {
+    need = ext_off + ext.list;
+    want = ext_off + ext.want();
+    if (noalloc && need > rl::kScratchBytes - rl::kScratchErrBytes) {
       route = false;
-      need = lay.total;
+      need = want = lay.total;
     }
   }
   WsView w{};
-  RL_TRY(get_ws(st, need, noalloc, &w));
+  RL_TRY(get_ws(st, need, want, route && ext.segmented, cus, noalloc, &w));
   char* base = w.ptr;
   a.q = q->data;
   a.q_sb = q->strides[0];
@@ -815,8 +838,8 @@ int decode_impl(const rl_tensor* q, const rl_tensor* k_pages, const rl_tensor* v
     rl::ExtendArgs x = extend_rows();
     x.staged = 1;
     x.gate = a.ws.hdr + 3;
-    const WsView xw{base + ext_off, w.err};
-    rc = run_extend(x, ext, st, 0, noalloc, &xw, room - ext_off, false);
+    const WsView xw{base + ext_off, w.size - ext_off, w.err, w.stash, w.stash_wgs};
+    rc = run_extend(x, ext, cus, st, 0, noalloc, &xw, false);
   }
   if (timer) (void)hipEventRecord(timer->stop, st);
   prof_commit(0, timer);
@@ -884,7 +907,7 @@ int extend_impl(const rl_tensor* q, const rl_tensor* qo_indptr, const rl_tensor*
   RL_TRY(current_cus(&cus));
   const ExtendLayout L =
       extend_layout(B, total_q, total_q, Hkv, Hq / Hkv, (int64_t)a.kv.max_pages * a.kv.page_size, cus);
-  return run_extend(a, L, st, 1);
+  return run_extend(a, L, cus, st, 1);
 }
 
 // ------------------------------------------------------------------- append
@@ -922,7 +945,7 @@ int append_impl(const rl_tensor* k_new, const rl_tensor* v_new, const rl_tensor*
   if (B == 0 || total_new == 0) return RL_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
   Workspace* w = nullptr;
-  RL_TRY(acquire_ws(st, 0, &w));          // the error word only
+  RL_TRY(acquire_ws(st, 0, 0, false, &w));          // the error word only
   rl::AppendArgs a{};
   a.k_new = k_new->data;
   a.v_new = v_new->data;
@@ -1133,7 +1156,7 @@ int rl_attn_check_device_errors(void* stream) {
 
 int rl_attn_reserve_workspace(size_t bytes, void* stream) {
   Workspace* w = nullptr;
-  return acquire_ws(static_cast<hipStream_t>(stream), bytes, &w);
+  return acquire_ws(static_cast<hipStream_t>(stream), bytes, bytes, false, &w);
 }
 
 size_t rl_attn_decode_workspace_size(int64_t batch, int64_t num_q_heads, int64_t num_kv_heads, int64_t max_pages,

@@ -149,6 +149,74 @@ def test_capture_without_reserved_workspace_is_refused():
     assert err is not None and err.status == "RL_ERR_WORKSPACE"
 
 
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+def test_capture_with_room_for_the_list_only(fp8):
+    """A workspace that holds a call's work list, but no partials of split keys, is enough under
+    capture: units stay whole, with the bits of the eager call that splits them."""
+    hq, hkv, ps, lens = 16, 2, 64, [20000, 40000, 300]
+    n = [40, 3, 300]
+    w = wl.custom(407, "extend", lens, q_lens=n, hq=hq, hkv=hkv, page_size=ps)
+    H.say(f"capture with a list-only workspace fp8={fp8}")
+    t = (wl.materialize_fp8 if fp8 else wl.materialize)(w, DEV)
+    pages = (t["k_pages"], t["v_pages"]) + ((t["k_scale"], t["v_scale"]) if fp8 else ())
+    width = t["block_table"].shape[1]
+    plan = ra.diag_extend_plan(lens, hq, hkv, width * ps, qo_indptr=w.qo_indptr)
+    assert plan["split_seqs"] > 0
+    need = ra.extend_workspace_size(w.batch, w.total_q, hq, hkv, 1, ps)       # the list alone
+    assert need < ra.extend_workspace_size(w.batch, w.total_q, hq, hkv, width, ps)
+    ext = ra.extend_fp8 if fp8 else ra.extend
+    dec = ra.decode_fp8 if fp8 else ra.decode
+    q1 = t["q"][:w.batch].contiguous()
+
+    def calls(out_e, out_d, stream=None):
+        ext(t["q"], t["qo_indptr"], *pages, t["block_table"], t["kv_lens"], t["scale"], out=out_e, stream=stream)
+        dec(q1, *pages, t["block_table"], t["kv_lens"], t["scale"], out=out_d, deterministic=True, stream=stream)
+
+    want_e, want_d = torch.empty_like(t["q"]), torch.empty_like(q1)
+    calls(want_e, want_d)
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    ra.reserve_workspace(need, stream=s)
+    out_e, out_d = torch.empty_like(t["q"]), torch.empty_like(q1)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        calls(out_e, out_d, stream=s)
+    for rep in range(3):
+        out_e.zero_()
+        out_d.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out_e.view(torch.int16), want_e.view(torch.int16)), f"extend, replay {rep}"
+        assert torch.equal(out_d.view(torch.int16), want_d.view(torch.int16)), f"deterministic decode, replay {rep}"
+    ref_o, _ = H.oracle_full(w, t)
+    H.compare(out_e, ref_o, what="captured whole units")
+    ra.check_device_errors(s)
+
+
+def test_workspace_of_the_largest_batch_serves_smaller_captured_ones():
+    """Reserved once for 1,100 sequences (more than the planner splits), used by a captured call of 3."""
+    hq, hkv, ps, n = 16, 2, 64, [1, 50, 100]
+    w = wl.custom(408, "extend", [17000, 33000, 100], q_lens=n, hq=hq, hkv=hkv, page_size=ps)
+    H.say("workspace of a larger batch")
+    t = wl.materialize(w, DEV)
+    width = t["block_table"].shape[1]
+    s = torch.cuda.Stream()
+    ra.reserve_workspace(ra.extend_workspace_size(1100, w.total_q, hq, hkv, width, ps), stream=s)
+    assert ra.diag_extend_plan(w.kv_lens, hq, hkv, width * ps, qo_indptr=w.qo_indptr)["split_seqs"] > 0
+    want, _ = H.run_extend(w, t)
+    out = torch.empty_like(t["q"])
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        ra.extend(t["q"], t["qo_indptr"], t["k_pages"], t["v_pages"], t["block_table"], t["kv_lens"], t["scale"],
+                  out=out, stream=s)
+    for rep in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), want.view(torch.int16)), f"replay {rep}"
+    ra.check_device_errors(s)
+
+
 def test_profiling_skips_captured_calls():
     """With kernel timing on, a call captured into a graph is not timed (its events
     would only be recorded at replay); eager calls still are."""

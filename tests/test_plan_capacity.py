@@ -350,18 +350,45 @@ def test_every_plan_is_complete_or_reported(seed):
 
 
 def test_extend_workspace_has_room_for_splits():
-    """The size query covers the list, the slots of split units and a running merge per
-    workgroup as soon as the block table holds more than a segment, and nothing of
-    them below that."""
+    """The size query covers the list and the slots of split units as soon as the block table
+    holds more than a segment, and nothing of them below that. (The running merges have
+    room of their own behind every workspace.)"""
     small = ra.extend_workspace_size(4, 100, 64, 8, SEGMENT // 64, 64)
     large = ra.extend_workspace_size(4, 100, 64, 8, SEGMENT // 64 + 1, 64)
     units = ra.diag_extend_capacity(4, 100, 64, 8)["max_items"]
     wave = 64 * 66 * 4
     assert small == 256 + align256(units * 16)
-    # two segments per unit, 8 waves per slot, and a merge state for each CU
-    assert large >= small + (2 * units + min(units, 256)) * 8 * wave
+    # two segments per unit, 8 waves per slot
+    assert large >= small + 2 * units * 8 * wave
     # the slots are bounded whatever the sizes
     assert ra.extend_workspace_size(1000, 100000, 64, 8, 16384, 64) < 2 ** 30
+
+
+BATCHES = [1, 2, 7, 64, 255, 512, 1000, 1023, 1024, 1025, 1026, 2048, 5000]
+
+
+@pytest.mark.parametrize("heads", [(8, 8), (32, 8), (64, 8), (96, 8), (7, 1), (200, 1)])
+def test_workspace_sizes_never_fall_as_a_call_grows(heads):
+    """A workspace reserved for the largest call serves every smaller one: batches across the
+    planner's split limit (1024), rows, tokens per sequence and block-table widths (both
+    sides of a segment)."""
+    hq, hkv = heads
+
+    def rising(sizes, what):
+        assert all(x <= y for x, y in zip(sizes, sizes[1:])), (what, sizes)
+
+    tables = [1, 255, 256, 257, 512, 513, 1024, 4096, 16384]
+    for pages in (100, 512, 2048):
+        for total in (1, 333, 4096, 100000):
+            rising([ra.extend_workspace_size(b, total, hq, hkv, pages, 64) for b in BATCHES], ("extend batch", total))
+        for tok in (1, 4, 64):
+            rising([ra.decode_workspace_size(b, hq, hkv, pages, 64, tok) for b in BATCHES], ("decode batch", tok))
+        rising([ra.extend_workspace_size(33, n, hq, hkv, pages, 64) for n in (1, 2, 3, 31, 32, 33, 255, 300, 5000, 70000)],
+               "rows")
+        rising([ra.decode_workspace_size(33, hq, hkv, pages, 64, n) for n in range(1, 65)], "tokens")
+    for b in (1, 40, 1024, 1500):
+        rising([ra.extend_workspace_size(b, 4096, hq, hkv, p, 64) for p in tables], "extend pages")
+        rising([ra.decode_workspace_size(b, hq, hkv, p, 64, 2) for p in tables], "decode pages")
 
 
 def test_capacity_model_reaches_its_bounds():
