@@ -53,10 +53,11 @@ int rl_attn_diag_extend_capacity(int64_t batch, int64_t total_q, int64_t num_q_h
  * `cus` compute units: the planner's own decisions, made on the host from host
  * arrays (no HIP call). qo_indptr holds batch + 1 entries (not read for
  * decode), kv_lens batch; max_tokens is the block table's room per sequence.
- * out[0..6] = work items listed, those of them that are parts of split units,
- * sequences split, split units that will be finished, how many of these lack a
- * part, the error bits of the input, the unit capacity. Returns RL_OK or
- * RL_ERR_INVALID_ARG. */
+ * out[0..7] = work items listed, those of them that are parts of split units,
+ * sequences split, split units with all of their parts, split units that lack
+ * one, the error bits of the input, the unit capacity, and what the kernel is
+ * told: 0 no row over more than 16384 keys, 1 some, 2 some and units split.
+ * Returns RL_OK or RL_ERR_INVALID_ARG. */
 int rl_attn_diag_extend_plan(const int32_t* qo_indptr, const int32_t* kv_lens, int64_t batch, int64_t total_q,
                              int64_t query_tokens, int64_t num_q_heads, int64_t num_kv_heads, int64_t max_tokens,
                              int32_t cus, int64_t* out);

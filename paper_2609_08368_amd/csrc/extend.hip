@@ -15,11 +15,11 @@
 // A row over more than kSegKeys keys is the in-order merge of one partial per
 // key segment. The planner splits a sequence's units at the segments where
 // whole units would leave CUs idle: then every (unit, segment) is an item that
-// leaves its partial in a slot, and merge_segments_kernel finishes the rows;
-// otherwise one workgroup takes all of a unit's keys and merges as it goes.
-// Both give the same bits. One 333-token turn behind 23.5K keys (64/8 heads: 88
-// units for 256 CUs): 486 -> 364 us per call; deterministic decode of 24
-// sequences of 1-32K keys (192 units): 604 -> 351 us.
+// leaves its partial in a slot, and the workgroup that brings a unit's last one
+// finishes its rows; otherwise one workgroup takes all of a unit's keys, segment
+// after segment. Both give the same bits. One 333-token turn behind 23.5K keys
+// (64/8 heads: 88 units for 256 CUs): 483 us a call with whole units, 355 split;
+// deterministic decode of 24 sequences of 1-32K keys (192 units): 603 and 332 us.
 #include <algorithm>
 #include <type_traits>
 #include <vector>
@@ -37,9 +37,9 @@ __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
   __shared__ int keys[kSortMax];
   __shared__ int slot_of[kSortMax];
   // of the sequences being emitted: (sequence, chunk rows, prefix, first slot or -1), (first item, items of one
-  // head group, first split unit)
+  // head group)
   __shared__ int4 seq_a[1024];
-  __shared__ int4 seq_b[1024];
+  __shared__ int2 seq_b[1024];
   __shared__ unsigned long long all_keys, all_units;
   __shared__ int wave_tot[16];
   const int tid = threadIdx.x;
@@ -83,12 +83,17 @@ __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
   const bool sorted = a.B <= kSortMax;
   const int heads = a.Hkv * a.head_blocks, tt = a.tile_tokens;
   auto tiles = [&](int n) { return unit_tiles(n, tt); };
+  // rows over several segments (then a workgroup per CU runs the list), and units split at them
+  bool any_long = false, any_split = false;
   if (sorted) {
-    const bool may_split = a.max_slots > 0;
     SeqRange r{0, 0, 0};
-    if (tid < a.B) r = seq_range(a, tid, &bad);
-    int need = 0;
-    if (may_split) {
+    if (tid < a.B) {
+      r = seq_range(a, tid, &bad);
+      keys[tid] = r.kv;
+      slot_of[tid] = -1;
+    }
+    any_long = __syncthreads_or(a.segmented && r.n > 0 && r.kv > kSegKeys);
+    if (any_long && a.max_slots > 0) {
       if (tid == 0) all_keys = all_units = 0;
       __syncthreads();
       if (r.n > 0) {
@@ -97,16 +102,16 @@ __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
         atomicAdd(&all_keys, units * r.kv);
       }
       __syncthreads();
-      need = split_need(a, r, all_keys, all_units);
+      const int need = tid < a.B ? split_need(a, r, all_keys, all_units) : 0;
+      int tot;
+      const int first = block_exclusive_scan(need, &tot, wave_tot);
+      const bool split = need > 0 && first + need <= a.max_slots;
+      if (split) {
+        slot_of[tid] = first;
+        keys[tid] = max(kSegKeys, r.kv / 2);   // about its longest item
+      }
+      any_split = __syncthreads_or(split);
     }
-    int tot, first = 0;
-    if (may_split) first = block_exclusive_scan(need, &tot, wave_tot);
-    const bool split = need > 0 && first + need <= a.max_slots;
-    if (tid < a.B) {
-      slot_of[tid] = split ? first : -1;
-      keys[tid] = split ? max(kSegKeys, r.kv / 2) : r.kv;   // about its longest item
-    }
-    __syncthreads();
     for (int b = tid; b < a.B; b += blockDim.x) {
       const int kb = keys[b];
       int rank = 0;
@@ -116,7 +121,7 @@ __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
     __syncthreads();
   }
   const bool xcd = kXcdGroups && heads % kXcds == 0;
-  int offset = 0, moffset = 0;
+  int offset = 0;
   for (int p0 = 0; p0 < a.B; p0 += blockDim.x) {
     const int p = p0 + tid;
     int per = 0, b = 0, slot = -1;
@@ -128,11 +133,11 @@ __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
       slot = sorted ? slot_of[b] : -1;
       per = slot >= 0 ? (int)unit_segments(r, tt) : tiles(r.n);
     }
-    int tot, mtot = 0, mexcl = 0;
+    if (!sorted && a.segmented) any_long |= __syncthreads_or(r.n > 0 && r.kv > kSegKeys) != 0;
+    int tot;
     const int excl = block_exclusive_scan(per * heads, &tot, wave_tot);
-    if (a.max_slots > 0) mexcl = block_exclusive_scan(slot >= 0 ? tiles(r.n) * heads : 0, &mtot, wave_tot);
     seq_a[tid] = make_int4(b, r.n, r.kv - r.n, slot);
-    seq_b[tid] = make_int4(offset + excl, per, moffset + mexcl, 0);
+    seq_b[tid] = make_int2(offset + excl, per);
     __syncthreads();
     // the items of a sequence are written by as many threads as the batch leaves
     // it (a wave each instead: draft batch of 96 x 8 units, 851 against 847 us a call)
@@ -140,16 +145,16 @@ __global__ __launch_bounds__(1024) void plan_extend_kernel(ExtendArgs a) {
     const int lps_log = 10 - (n_seq > 1 ? 32 - __builtin_clz((unsigned)(n_seq - 1)) : 0);
     const int lps = 1 << lps_log, s = tid >> lps_log;
     if (s < n_seq) {
-      const int4 sa = seq_a[s], sb = seq_b[s];
-      const SeqPlan plan{sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z};
-      for (int i = tid & (lps - 1); i < sb.y * heads; i += lps) bad |= place_item(a, plan, i, xcd);
+      const int4 sa = seq_a[s];
+      const int2 sb = seq_b[s];
+      const SeqPlan plan{sa.x, sa.y, sa.z, sa.w, sb.x, sb.y};
+      for (int i = tid & (lps - 1); i < sb.y * heads; i += lps) bad |= place_item(a, plan, i, xcd, any_split);
     }
     offset += tot;
-    moffset += mtot;
-    __syncthreads();                     // the lists are rebuilt for the next pass
+    if (p0 + (int)blockDim.x < a.B) __syncthreads();   // the lists are rebuilt for the next pass
   }
-  if (tid == 0) a.ws.hdr[0] = offset < a.max_items ? offset : a.max_items;
-  if (tid == 1) a.ws.hdr[1] = moffset;
+  if (tid == 0) a.ws.hdr[0] = min(offset, list_room(a, any_split));
+  if (tid == 1) a.ws.hdr[1] = any_split ? kSplit : any_long ? kSegments : kOneSegment;
   if (tid < kXcds) a.ws.hdr[8 + tid] = (a.workers + kXcds - 1 - tid) / kXcds;
   if (bad) atomicOr(a.ws.err, bad);
 }
@@ -188,169 +193,198 @@ __device__ __forceinline__ UnitRow unit_row(const ExtendArgs& a, int r, int cnt,
   return {ok, ti, g * a.R + hb * RB + (ok ? hi : 0)};
 }
 
-template <bool kFp8, int kPages, bool kNt, bool kSeg>
-__global__ __launch_bounds__(kExtWaves * 64, 2) void extend_mfma_kernel(ExtendArgs args) {
-  // Units run in list order (longest key range first). Workgroups are handed
-  // to the XCDs round-robin, so each XCD takes every eighth entry; the planner
-  // lays the list out so those are the units of the (sequence, KV head) groups
-  // assigned to that XCD, which then share their keys through its L2.
-  // Segmented calls run a workgroup per CU that takes units until the list is
-  // empty (a running merge each; 39.9 against 41.1 ms with a workgroup per unit
-  // on the multi-turn batch, same kernel); the others keep a workgroup per
-  // unit, which small units start faster on.
-  __shared__ int next_unit;
-  const int n_units = args.ws.hdr[0];
+// Joins a split unit's partials in key order, as a workgroup that has all of the
+// unit's segments does (row block `wave` of the unit). slot0: the slot of segment 0.
+__device__ __forceinline__ void join_parts(const ExtendArgs& a, int slot0, int n_seg, int prefix, int n, int wave,
+                                           f32x16 (&o)[4], float& m, float& l) {
+  int slot = slot0;
+  for (int s = 0; s < n_seg; ++s) {
+    const StateWord* p = (const StateWord*)a.ws.part + ((size_t)slot * a.slot_waves + wave) * kSegWaveFloats;
+    if (s == 0)
+      seg_load(p, o, m, l);
+    else
+      seg_join(p, o, m, l);
+    if (s + 1 < n_seg) slot -= segment_tiles(s + 1, prefix, n, unit_tiles(n, a.tile_tokens), a.tile_tokens);
+  }
+}
+
+// The LDS of a workgroup. The K and V buffers of the 128-key steps are arrays of
+// their own (see tile_attn.hpp).
+struct DirectLds {
+  char *kl0, *kl1, *vl0, *vl1;
+};
+
+// One list entry `it` (its place: unit): attention of the unit's rows over all
+// of its keys, or over one segment of a split unit. kSeg: the call has rows over
+// several segments (mode: kSegments or kSplit) and the next unit of this
+// workgroup is left in *next_unit. kSeg = false is the plain run over the keys.
+template <bool kFp8, int kPages, bool kNt, bool kSeg, typename Lds>
+__device__ __forceinline__ void extend_unit(const ExtendArgs& a, int unit, const int4 it, int mode, int n_units,
+                                            const Lds& lds, int* next_unit, int* parts_here) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int swave = __builtin_amdgcn_readfirstlane(wave);
-  int unit = blockIdx.x;    // (a worker's first unit needs no counter: the planner starts them behind these)
-  // every pass takes a new entry of a finite list, so the loop ends
-  while (unit < n_units) {
-    // The arguments are read again for each unit (the empty asm hides that
-    // they are the same): kept over the loop they would not fit the scalar
-    // registers beside a unit's own values.
-    typedef __attribute__((address_space(4))) const ExtendArgs ConstArgs;
-    ConstArgs* ap = (ConstArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(ap));
-    const ExtendArgs a = *(const ExtendArgs*)ap;
-    const int4 it = a.ws.items[unit];
-    const int2 part = kSeg && a.ws.segs ? a.ws.segs[unit] : make_int2(-1, -1);
-    const int b = it.x, i0 = it.y, cnt = it.z, g = it.w & 0xffff, hb = it.w >> 16;
-    int bad_seq = 0, bad = 0;               // sequence errors are reported by the planner
-    const SeqRange sr = seq_range(a, b, &bad_seq);
-    const int prefix = sr.kv - sr.n;
-    const int t_unit = prefix + i0 + cnt;    // keys [0, t_unit) are visible to some row
-    const int t_full = prefix + i0;          // keys [0, t_full) are visible to every row
-    const int t_lo = segment_start(part.x);
-    const int t_end = part.x >= 0 && part.x + 1 < segment_count(t_unit) ? segment_start(part.x + 1) : t_unit;
+  const int2 part = kSeg && mode == kSplit ? a.ws.segs[unit] : make_int2(-1, -1);
+  const int b = it.x, i0 = it.y, cnt = it.z, g = it.w & 0xffff, hb = it.w >> 16;
+  int bad_seq = 0, bad = 0;               // sequence errors are reported by the planner
+  const SeqRange sr = seq_range(a, b, &bad_seq);
+  const int prefix = sr.kv - sr.n;
+  const int t_unit = prefix + i0 + cnt;    // keys [0, t_unit) are visible to some row
+  const int t_full = prefix + i0;          // keys [0, t_full) are visible to every row
+  // segments [seg, seg_end) of the unit's n_seg: one of a split unit, else all
+  const int n_seg = kSeg ? segment_count(t_unit) : 1;
+  int seg = part.x >= 0 ? part.x : 0;
+  const int seg_end = part.x >= 0 ? part.x + 1 : n_seg;
 
-    const UnitRow row = unit_row(a, wave * kWaveRows + (lane & 31), cnt, g, hb);
-    const int limit = row.ok ? prefix + i0 + row.ti : t_unit - 1;
-    const int64_t qrow = sr.q0 + i0 + (row.ok ? row.ti : 0);
+  const UnitRow row = unit_row(a, wave * kWaveRows + (lane & 31), cnt, g, hb);
+  const int limit = row.ok ? prefix + i0 + row.ti : t_unit - 1;
+  const int64_t qrow = sr.q0 + i0 + (row.ok ? row.ti : 0);
 
-    bf16x8 qv[8];
-    load_q_operand((const __bf16*)a.q + qrow * a.q_st + (int64_t)row.head * a.q_sh, row.ok, qv);
-    f32x16 o[4];
+  bf16x8 qv[8];
+  load_q_operand((const __bf16*)a.q + qrow * a.q_st + (int64_t)row.head * a.q_sh, row.ok, qv);
+  int bad_scale = 0;
+  // the K dequantisation scale joins the softmax scale, the V scale the output
+  const KvScales dq = kv_scales<kFp8>(a.kv, g, &bad_scale);
+  const float scale = a.scale * dq.k;
+  const int* bt_row = a.kv.bt + (int64_t)b * a.kv.bt_sb;
+  // a wave whose 32 rows are all past the unit's tokens (a short chunk, or
+  // the one token of a deterministic decode) only stages
+  const bool active = __builtin_amdgcn_ballot_w64(row.ok) != 0;
+  f32x16 o[4];
+  float m_run, l_run;
+  for (;;) {
+    const int t_lo = segment_start(seg);
+    const int t_end = seg + 1 < n_seg ? segment_start(seg + 1) : t_unit;
 #pragma unroll
     for (int jd = 0; jd < 4; ++jd)
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[jd][e] = 0.f;
-    float m_run = t_lo > 0 ? kNoKey : kNegInf, l_run = 0.f;
-    int bad_scale = 0;
-    // the K dequantisation scale joins the softmax scale, the V scale the output
-    const KvScales dq = kv_scales<kFp8>(a.kv, g, &bad_scale);
-    const float scale = a.scale * dq.k;
-    const int* bt_row = a.kv.bt + (int64_t)b * a.kv.bt_sb;
-    // a wave whose 32 rows are all past the unit's tokens (a short chunk, or
-    // the one token of a deterministic decode) only stages
-    const bool active = __builtin_amdgcn_ballot_w64(row.ok) != 0;
-    float* stash = a.ws.stash + ((size_t)blockIdx.x * a.slot_waves + swave) * kSegWaveFloats;
-    if constexpr (kPages == kDirectPages) {
-      static_assert(!kFp8, "rows go to LDS as stored: bf16 pages only");
-      __shared__ __attribute__((aligned(16))) char kl0[kDlKBytes], kl1[kDlKBytes], vl0[kDlVBytes], vl1[kDlVBytes];
-      if (active)
-        tile_attend_dl<true, kNt, kSeg>(a.kv, scale, bt_row, g, t_lo, t_end, t_full, limit, qv, kl0, kl1, vl0, vl1, o,
-                                  m_run, l_run, bad, stash);
-      else
-        tile_attend_dl<false, kNt, kSeg>(a.kv, scale, bt_row, g, t_lo, t_end, t_full, limit, qv, kl0, kl1, vl0, vl1, o,
-                                   m_run, l_run, bad, stash);
-    } else {
-      __shared__ TileLds lds;
-      auto attend = [&](auto compute_tag) {
-        constexpr bool kC = decltype(compute_tag)::value;
-        tile_attend_pp<kExtWaves, kPages != kRowPages, kFp8, kC, kPages == kSetPages, kNt, kSeg>(
-            a.kv, scale, bt_row, g, t_lo, t_end, t_full, limit, qv, lds, o, m_run, l_run, bad, stash);
-      };
-      if (active)
-        attend(std::true_type{});
-      else
-        attend(std::false_type{});
-    }
-    // the next unit is taken only now, so that no worker holds one it cannot start
-    if (kSeg && threadIdx.x == 0) next_unit = take_unit(a.ws.hdr + 8, n_units);
-
-    if (kSeg && part.y >= 0) {
-      if (active) seg_store(a.ws.part + ((size_t)part.y * a.slot_waves + swave) * kSegWaveFloats, o, m_run, l_run);
-    } else {
-      if (kSeg && active && t_unit > kSegKeys) seg_merge(stash, o, m_run, l_run);
-      const float l_tot = sum_l32(l_run);
-      if (row.ok) {
-        const float inv = l_tot > 0.f ? dq.v / l_tot : 0.f;
-        if (a.out_f32)
-          store_o_row((float*)a.out + qrow * a.out_st + (int64_t)row.head * a.out_sh, o, inv);
-        else
-          store_o_row((__bf16*)a.out + qrow * a.out_st + (int64_t)row.head * a.out_sh, o, inv);
-        if (a.lse && lane < 32)
-          a.lse[qrow * a.lse_st + (int64_t)row.head * a.lse_sh] =
-              l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : kNegInf;
+    m_run = kSeg && seg > 0 ? kNoKey : kNegInf;
+    l_run = 0.f;
+    auto attend = [&](auto compute_tag) {
+      constexpr bool kC = decltype(compute_tag)::value;
+      if constexpr (kPages == kDirectPages) {
+        static_assert(!kFp8, "rows go to LDS as stored: bf16 pages only");
+        tile_attend_dl<kC, kNt>(a.kv, scale, bt_row, g, t_lo, t_end, t_full, limit, qv, lds.kl0, lds.kl1, lds.vl0,
+                                lds.vl1, o, m_run, l_run, bad);
+      } else {
+        tile_attend_pp<kExtWaves, kPages != kRowPages, kFp8, kC, kPages == kSetPages, kNt>(
+            a.kv, scale, bt_row, g, t_lo, t_end, t_full, limit, qv, *lds, o, m_run, l_run, bad);
       }
-    }
-    if (bad) atomicOr(a.ws.err, kErrPage);
-    if (bad_scale) atomicOr(a.ws.err, kErrScale);
+    };
+    if (active)
+      attend(std::true_type{});
+    else
+      attend(std::false_type{});
     if constexpr (!kSeg) break;
-    // the LDS tiles are free and next_unit is written; it is read before the
-    // next unit's barriers, which every wave passes before the next write
-    __syncthreads();
-    unit = __builtin_amdgcn_readfirstlane(next_unit);
+    if (part.x >= 0 || n_seg == 1) break;
+    // all segments of the unit are this workgroup's: they join the running
+    // merge (its address is hidden from the compiler, which would otherwise form
+    // it before the segments and spill: 133 instead of 115 us for 128 x 1K rows)
+    StateWord* stash = (StateWord*)a.ws.stash + ((size_t)blockIdx.x * a.slot_waves + swave) * kSegWaveFloats;
+    asm volatile("" : "+s"(stash));
+    if (active) {
+      if (seg > 0) seg_merge(stash, o, m_run, l_run);
+      if (seg + 1 < seg_end) seg_store(stash, o, m_run, l_run);
+    }
+    if (++seg == seg_end) break;
+    __syncthreads();                       // the LDS tiles are free
   }
+  // the next unit is taken only now, so that no worker holds one it cannot start
+  if (kSeg && threadIdx.x == 0) *next_unit = take_unit(a.ws.hdr + 8, n_units);
+
+  bool finish = true;
+  if (kSeg && part.x >= 0) {
+    // A part of a split unit goes to its slot, and the workgroup that brings
+    // the last one finishes the rows; none waits, and a unit that lacks a part
+    // is left unwritten. Once the barrier has seen every wave's stores
+    // complete, one thread makes them visible to the device, counts, and for the last part
+    // takes in the others' (a release by each wave cost 7% on the ragged
+    // deterministic decode: it writes the XCD's L2 back).
+    int slot0 = part.y;
+    for (int s = 1; s <= part.x; ++s) slot0 = slot_before(slot0, s, prefix, sr.n, a.tile_tokens);
+    StateWord* mine = (StateWord*)a.ws.part + ((size_t)part.y * a.slot_waves + swave) * kSegWaveFloats;
+    asm volatile("" : "+s"(mine));         // (as the stash's)
+    if (active) seg_store(mine, o, m_run, l_run);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      const int n = __hip_atomic_fetch_add(&a.ws.arrived[slot0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+      if (n == n_seg) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      *parts_here = n;
+    }
+    __syncthreads();
+    finish = __builtin_amdgcn_readfirstlane(*parts_here) == n_seg;
+    if (finish && active) join_parts(a, slot0, n_seg, prefix, sr.n, swave, o, m_run, l_run);
+  }
+  if (finish) {
+    const float l_tot = sum_l32(l_run);
+    if (row.ok) {
+      const float inv = l_tot > 0.f ? dq.v / l_tot : 0.f;
+      if (a.out_f32)
+        store_o_row((float*)a.out + qrow * a.out_st + (int64_t)row.head * a.out_sh, o, inv);
+      else
+        store_o_row((__bf16*)a.out + qrow * a.out_st + (int64_t)row.head * a.out_sh, o, inv);
+      if (a.lse && lane < 32)
+        a.lse[qrow * a.lse_st + (int64_t)row.head * a.lse_sh] =
+            l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : kNegInf;
+    }
+  }
+  if (bad) atomicOr(a.ws.err, kErrPage);
+  if (bad_scale) atomicOr(a.ws.err, kErrScale);
 }
 
-// Finishes the rows of split units: merges their segments' partials in key
-// order, as seg_flush does for whole units. A wave takes 32 dimensions of 32
-// rows (block jd of the wave's state), so the elements it merges and the
-// weights are those of the whole-unit merge.
-template <bool kFp8>
-__global__ __launch_bounds__(256) void merge_segments_kernel(ExtendArgs a) {
-  const int n = a.ws.hdr[1] * a.slot_waves;
-  const int lane = threadIdx.x & 63;
-  const int jd = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int wi = blockIdx.x; wi < n; wi += gridDim.x) {
-    const int u = wi / a.slot_waves, w = wi - u * a.slot_waves;
-    const int4 it = a.ws.munits[u];
-    const int2 ms = a.ws.mslots[u];
-    const int b = it.x, i0 = it.y, cnt = it.z, g = it.w & 0xffff, hb = it.w >> 16;
-    const UnitRow row = unit_row(a, w * kWaveRows + (lane & 31), cnt, g, hb);
-    if (__builtin_amdgcn_ballot_w64(row.ok) == 0) continue;
-    int dummy = 0;
-    const SeqRange sr = seq_range(a, b, &dummy);
-    const int prefix = sr.kv - sr.n, nt = (sr.n + a.tile_tokens - 1) / a.tile_tokens;
-    const int n_seg = segment_count(prefix + i0 + cnt);
-    f32x16 o;
-    float m = 0.f, l = 0.f;
-    int slot = ms.x + ms.y;
-    for (int s = 0; s < n_seg; ++s) {
-      const float* p = a.ws.part + ((size_t)slot * a.slot_waves + w) * kSegWaveFloats;
-      slot -= segment_tiles(s + 1, prefix, sr.n, nt, a.tile_tokens);
-      const float m1 = p[4096 + lane], l1 = p[4160 + lane];
-      f32x4 x[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = *reinterpret_cast<const f32x4*>(p + 256 * (4 * jd + i) + 4 * lane);
-      if (s == 0) {
-        m = m1;
-        l = l1;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) o[e] = x[e >> 2][e & 3];
-      } else {
-        const SegWeights sw = seg_weights(m, m1, sum_l32(l1));
-        l = seg_mix(l, l1, sw);
-        m = sw.m;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) o[e] = seg_mix(o[e], x[e >> 2][e & 3], sw);
+// Units run in list order (longest key range first). Workgroups are handed
+// to the XCDs round-robin, so each XCD takes every eighth entry; the planner
+// lays the list out so those are the units of the (sequence, KV head) groups
+// assigned to that XCD, which then share their keys through its L2.
+//
+// The planner, which knows the lengths, decides how the list is run. With no row
+// over more than a segment: a workgroup per unit and the plain routine, whatever
+// the block table's width (with the segments' routine for both, calls of short
+// rows took 1-3% longer: 115.0 against 113.5 us for a deterministic decode of 128
+// x 1K keys, 34.9 and 34.1 for two 64-token chunks). With such rows: a workgroup
+// per CU, each with one running merge, takes units until the list is empty
+// (multi-turn batch 40.2 ms against 42.0 with a workgroup per unit and no
+// segments); the rest of the grid ends at once.
+template <bool kFp8, int kPages, bool kNt>
+__global__ __launch_bounds__(kExtWaves * 64, 2) void extend_mfma_kernel(ExtendArgs args) {
+  __shared__ int next_unit, parts_here;
+  // (read beside the header: the grid is no larger than the list's room)
+  int4 it = args.ws.items[blockIdx.x];
+  const int n_units = args.ws.hdr[0], mode = args.ws.hdr[1];
+  int unit = blockIdx.x;    // (a worker's first unit needs no counter: the planner starts them behind these)
+  auto run = [&](const auto& lds) {
+    // (this branch first: laid out behind the other, the 64-key step loops of
+    // long rows ran 1-2% slower)
+    if (__builtin_expect(mode != kOneSegment, 1)) {
+      if (unit >= args.workers) return;
+      // every pass takes a new entry of a finite list, so the loop ends
+      while (unit < n_units) {
+        // The arguments are read again for each unit (the empty asm hides that
+        // they are the same): kept over the loop they would not fit the scalar
+        // registers beside a unit's own values.
+        typedef __attribute__((address_space(4))) const ExtendArgs ConstArgs;
+        ConstArgs* ap = (ConstArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(ap));
+        const ExtendArgs a = *(const ExtendArgs*)ap;
+        extend_unit<kFp8, kPages, kNt, true>(a, unit, it, mode, n_units, lds, &next_unit, &parts_here);
+        // the LDS tiles are free and next_unit is written; it is read before the
+        // next unit's barriers, which every wave passes before the next write
+        __syncthreads();
+        unit = __builtin_amdgcn_readfirstlane(next_unit);
+        if (unit < n_units) it = a.ws.items[unit];
       }
+    } else if (unit < n_units) {
+      extend_unit<kFp8, kPages, kNt, false>(args, unit, it, mode, n_units, lds, &next_unit, &parts_here);
     }
-    const float l_tot = sum_l32(l);
-    if (row.ok) {
-      const int64_t qrow = sr.q0 + i0 + row.ti;
-      const KvScales dq = kv_scales<kFp8>(a.kv, g, &dummy);
-      const float inv = l_tot > 0.f ? dq.v / l_tot : 0.f;
-      const int64_t off = qrow * a.out_st + (int64_t)row.head * a.out_sh;
-      if (a.out_f32)
-        store_o_block((float*)a.out + off, o, jd, inv);
-      else
-        store_o_block((__bf16*)a.out + off, o, jd, inv);
-      if (a.lse && jd == 0 && lane < 32)
-        a.lse[qrow * a.lse_st + (int64_t)row.head * a.lse_sh] =
-            l_tot > 0.f ? (m + __builtin_amdgcn_logf(l_tot)) * kLn2 : kNegInf;
-    }
+  };
+  if constexpr (kPages == kDirectPages) {
+    __shared__ __attribute__((aligned(16))) char kl0[kDlKBytes], kl1[kDlKBytes], vl0[kDlVBytes], vl1[kDlVBytes];
+    run(DirectLds{kl0, kl1, vl0, vl1});
+  } else {
+    __shared__ TileLds lds;
+    run(&lds);
   }
 }
 
@@ -384,24 +418,27 @@ int plan_extend_on_host(const ExtendArgs& a, int* split_seqs) {
     }
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return keys[x] > keys[y]; });
   }
-  int offset = 0, moffset = 0;
+  bool any_long = false;
+  for (const SeqRange& x : r) any_long = any_long || (a.segmented && x.n > 0 && x.kv > kSegKeys);
+  int offset = 0;
   for (int p = 0; p < a.B; ++p) {
     const SeqRange& s = r[order[p]];
     const int slot = slot_of[order[p]];
     const int per = slot >= 0 ? (int)unit_segments(s, a.tile_tokens) : unit_tiles(s.n, a.tile_tokens);
-    const SeqPlan plan{order[p], s.n, s.kv - s.n, slot, offset, per, moffset};
-    for (int i = 0; i < per * heads; ++i) bad |= place_item(a, plan, i, kXcdGroups && heads % kXcds == 0);
+    const SeqPlan plan{order[p], s.n, s.kv - s.n, slot, offset, per};
+    for (int i = 0; i < per * heads; ++i)
+      bad |= place_item(a, plan, i, kXcdGroups && heads % kXcds == 0, *split_seqs > 0);
     offset += per * heads;
-    if (slot >= 0) moffset += unit_tiles(s.n, a.tile_tokens) * heads;
   }
-  a.ws.hdr[0] = offset < a.max_items ? offset : a.max_items;
-  a.ws.hdr[1] = moffset;
+  a.ws.hdr[0] = std::min(offset, list_room(a, *split_seqs > 0));
+  a.ws.hdr[1] = *split_seqs > 0 ? kSplit : any_long ? kSegments : kOneSegment;
   return bad;
 }
 
 hipError_t launch_extend(const ExtendArgs& a, hipStream_t stream, KernelTimer* timer) {
   plan_extend_kernel<<<1, 1024, 0, stream>>>(a);
-  const unsigned grid = (unsigned)(a.segmented ? a.workers : a.max_items);
+  // a workgroup per unit, or per worker (the device decides; both at most max_items)
+  const unsigned grid = (unsigned)std::max(a.max_items - a.max_slots, a.workers);
   if (timer) (void)hipEventRecord(timer->start, stream);
   const bool scalar_ids = scalar_page_offsets(a.kv);
   const int pages = !scalar_ids ? kRowPages : (a.kv.page_size >= kKeys ? kStepPages : kSetPages);
@@ -409,45 +446,38 @@ hipError_t launch_extend(const ExtendArgs& a, hipStream_t stream, KernelTimer* t
   // every key row is read once, so the rows are loaded non-temporally (pages
   // of at least a step only)
   const bool once = a.decode_rows > 0 && a.head_blocks == 1 && a.decode_rows <= a.tile_tokens;
-  // (the segmented kernels are instances of their own: the merge's registers
-  // slowed the others' step loop by 4%, draft batch 852 against 885 us)
-  auto go = [&](auto fp8_tag, auto seg_tag) {
-    constexpr bool kF = decltype(fp8_tag)::value, kSeg = decltype(seg_tag)::value;
+  auto go = [&](auto fp8_tag) {
+    constexpr bool kF = decltype(fp8_tag)::value;
     auto launch = [&](auto pages_tag, auto nt_tag) {
-      extend_mfma_kernel<kF, decltype(pages_tag)::value, decltype(nt_tag)::value, kSeg>
+      extend_mfma_kernel<kF, decltype(pages_tag)::value, decltype(nt_tag)::value>
           <<<grid, kExtWaves * 64, 0, stream>>>(a);
     };
     const std::true_type nt{};
     const std::false_type cached{};
-    bool direct = false;
     if constexpr (!kF) {
-      direct = pages == kStepPages && !a.staged;
-      const std::integral_constant<int, kDirectPages> p{};
-      if (direct && once)
-        launch(p, nt);
-      else if (direct)
-        launch(p, cached);
+      if (pages == kStepPages && !a.staged) {
+        const std::integral_constant<int, kDirectPages> direct{};
+        if (once)
+          launch(direct, nt);
+        else
+          launch(direct, cached);
+        return;
+      }
     }
     const std::integral_constant<int, kStepPages> step{};
-    if (direct) {
-    } else if (pages == kStepPages && once) {
+    if (pages == kStepPages && once)
       launch(step, nt);
-    } else if (pages == kStepPages) {
+    else if (pages == kStepPages)
       launch(step, cached);
-    } else if (pages == kSetPages) {
+    else if (pages == kSetPages)
       launch(std::integral_constant<int, kSetPages>{}, cached);
-    } else {
+    else
       launch(std::integral_constant<int, kRowPages>{}, cached);
-    }
-    if (a.max_slots > 0)
-      merge_segments_kernel<kF><<<(unsigned)std::min(4 * a.workers, a.max_slots * a.slot_waves), 256, 0, stream>>>(a);
   };
-  const std::true_type yes{};
-  const std::false_type no{};
   if (a.kv.k_scale)
-    a.segmented ? go(yes, yes) : go(yes, no);
+    go(std::true_type{});
   else
-    a.segmented ? go(no, yes) : go(no, no);
+    go(std::false_type{});
   if (timer) (void)hipEventRecord(timer->stop, stream);
   return hipGetLastError();
 }

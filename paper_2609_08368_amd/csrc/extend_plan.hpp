@@ -91,21 +91,26 @@ inline __host__ __device__ int split_need(const ExtendArgs& a, const SeqRange& r
 }
 
 // A sequence in the list: its items start at `first`, `per` for each head
-// group; its slots start at `slot` (-1: its units are whole) and its split
-// units at `munit`.
+// group; its slots start at `slot` (-1: its units are whole).
 struct SeqPlan {
   int b, n, prefix, slot;
-  int first, per, munit;
+  int first, per;
 };
 
-// Writes item i of a sequence. With a multiple of 8 head groups (xcd), group gh
+// Entries of the list (a call that splits no unit has one for each).
+inline __host__ __device__ int list_room(const ExtendArgs& a, bool parts) {
+  return parts ? a.max_items : a.max_items - a.max_slots;
+}
+
+// Writes item i of a sequence (its part too, if the call splits any). With a multiple of 8 head groups (xcd), group gh
 // of a sequence runs on XCD gh % 8: its units share their keys through that
 // XCD's L2 instead of every XCD streaming every group's keys. Each XCD's units
 // stay in list order (longest first), and every XCD gets the same number of units.
-inline __host__ __device__ int place_item(const ExtendArgs& a, const SeqPlan& s, int i, bool xcd) {
+inline __host__ __device__ int place_item(const ExtendArgs& a, const SeqPlan& s, int i, bool xcd, bool parts) {
   const int tt = a.tile_tokens, nt = unit_tiles(s.n, tt);
-  const int gh = i / s.per, u = i - gh * s.per;
-  const int g = gh / a.head_blocks, hb = gh - g * a.head_blocks;
+  // (the tests spare a decode's items, one a head group, the divisions)
+  const int gh = s.per == 1 ? i : i / s.per, u = i - gh * s.per;
+  const int g = a.head_blocks == 1 ? gh : gh / a.head_blocks, hb = gh - g * a.head_blocks;
   // last tile first: it has the longest key range of the sequence; a
   // split sequence's items go segment by segment, so that the tiles
   // that read the same keys are neighbours, the last (longest) first
@@ -124,14 +129,18 @@ inline __host__ __device__ int place_item(const ExtendArgs& a, const SeqPlan& s,
   const int4 unit = make_int4(s.b, i0, tt < s.n - i0 ? tt : s.n - i0, g | (hb << 16));
   // beyond the list (chunks that overlap, so only with an invalid qo_indptr; their
   // count may even pass 31 bits): reported, never dropped silently
-  if ((unsigned)idx >= (unsigned)a.max_items) return kErrCapacity;
+  if ((unsigned)idx >= (unsigned)list_room(a, parts)) return kErrCapacity;
   a.ws.items[idx] = unit;
-  if (a.ws.segs) a.ws.segs[idx] = make_int2(seg, seg < 0 ? -1 : s.slot + i);
-  if (seg == 0) {              // every tile reaches into segment 0
-    a.ws.munits[s.munit + gh * nt + j] = unit;
-    a.ws.mslots[s.munit + gh * nt + j] = make_int2(s.slot + (gh + 1) * s.per - nt, j);
+  if (parts) {
+    a.ws.segs[idx] = make_int2(seg, seg < 0 ? -1 : s.slot + i);
+    if (seg == 0) a.ws.arrived[s.slot + i] = 0;    // (every tile reaches into segment 0)
   }
   return 0;
+}
+
+// Slot of a split unit's segment s - 1, given that of its segment s.
+inline __host__ __device__ int slot_before(int slot, int s, int prefix, int n, int tt) {
+  return slot + segment_tiles(s, prefix, n, unit_tiles(n, tt), tt);
 }
 
 // The planner on host arrays (a.ws, a.qo_indptr and a.kv_lens in host memory):

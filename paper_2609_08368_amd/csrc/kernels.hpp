@@ -128,6 +128,8 @@ struct DecodeArgs {
 // decode up to 32K keys took 351 us with doubling segments from 4096 or 8192
 // (602 before), and a turn of 333 tokens behind 23.5K 313 and 388 (483). From
 // 16384: 351 and 364 us, and 40.36 ms on the multi-turn batch (40.32 before).
+// (These with the boundary as a step of the loop; with a run per segment, from
+// 16384, 334 and 356 us and 38.7 ms beside 39.6 before.)
 constexpr int kSegKeys = 16384;
 inline __host__ __device__ int segment_start(int s) { return s > 0 ? kSegKeys << (s - 1) : 0; }
 // segments of a row over n > 0 keys
@@ -140,17 +142,19 @@ constexpr int kSplitBatchMax = 1024;
 constexpr int kSegWaveFloats = 64 * 66;
 
 struct ExtendPlanWs {
-  int* hdr;        // [0] work units, [1] split units, [8..15] next entry of each of the eight interleaved lists
+  int* hdr;        // [0] work items, [1] kOneSegment, kSegments or kSplit, [8..15] next entries of the eight lists
   int4* items;     // [max_items] (sequence, first chunk row, chunk rows, KV head | head block << 16)
   // null when the call's keys cannot be split: (segment, slot) of each item;
-  // segment -1: all of the unit's keys
+  // segment -1: all of the unit's keys. Written where hdr[1] is kSplit
   int2* segs;
-  int4* munits;    // [min(max_slots, units)] split units, as items
-  int2* mslots;    // (first slot of the unit's head group, the unit's place in its segments)
+  int* arrived;    // [max_slots] parts of a split unit that are in memory, at the slot of its segment 0
   float* part;     // [max_slots, slot_waves, kSegWaveFloats] partials of split units
   float* stash;    // [workers, slot_waves, kSegWaveFloats] running merges of unsplit units
   int* err;
 };
+// What the planner found (hdr[1] of an extend work list): no row over more than
+// one segment, rows over several, or such rows with units split at them.
+constexpr int kOneSegment = 0, kSegments = 1, kSplit = 2;
 
 struct ExtendArgs {
   PagedKV kv;
@@ -172,9 +176,10 @@ struct ExtendArgs {
   int max_items;
   int max_slots;          // partials of split units (0: no unit is split)
   int slot_waves;         // waves of a unit that hold rows, at most
-  int workers;            // workgroups that take units from the list until it is empty
-  // rows over more than kSegKeys keys are merged from segments; off where the
-  // block table has room for no more keys, and with `staged` steps (see there)
+  int workers;            // workgroups that take units from the list until it is empty, if rows have several segments
+  // rows over more than kSegKeys keys are merged from segments (whether there are
+  // any is for the planner to find); off where the block table has room for no
+  // more keys, and with `staged` steps (see there)
   int segmented;
   // n > 0: decode through the extend kernel: sequence b owns query rows
   // b n .. b n + n - 1, its last n keys (none if kv_lens[b] == 0; qo_indptr is

@@ -570,7 +570,7 @@ constexpr int64_t kSlotBytes = int64_t(256) << 20;
 struct ExtendLayout {
   int max_units, max_slots, slot_waves, workers;
   bool segmented;
-  size_t off_munits, off_mslots, off_segs, off_part, list, total;
+  size_t off_arrived, off_segs, off_part, list, total;
   size_t want() const { return max_slots > 0 ? total : list; }
 };
 
@@ -593,10 +593,8 @@ ExtendLayout extend_layout(int64_t B, int64_t total_q, int64_t row_tokens, int64
     const int64_t part_bytes = std::min<int64_t>(kSlotBytes, slots * slot_bytes);
     if (B <= rl::kSplitBatchMax) L.max_slots = (int)(part_bytes / slot_bytes);
     size_t off = 256 + align256((size_t)(L.max_units + slots) * 16);
-    L.off_munits = off;
-    off += align256((size_t)slots * 16);
-    L.off_mslots = off;
-    off += align256((size_t)slots * 8);
+    L.off_arrived = off;
+    off += align256((size_t)slots * 4);
     L.off_segs = off;
     off += align256((size_t)(L.max_units + slots) * 8);
     L.off_part = off;
@@ -639,15 +637,14 @@ int run_extend(rl::ExtendArgs& a, const ExtendLayout& L, int cus, hipStream_t st
   a.ws.hdr = reinterpret_cast<int*>(base);
   a.ws.items = reinterpret_cast<int4*>(base + 256);
   if (splits) {
-    a.ws.munits = reinterpret_cast<int4*>(base + L.off_munits);
-    a.ws.mslots = reinterpret_cast<int2*>(base + L.off_mslots);
+    a.ws.arrived = reinterpret_cast<int*>(base + L.off_arrived);
     a.ws.segs = reinterpret_cast<int2*>(base + L.off_segs);
     a.ws.part = reinterpret_cast<float*>(base + L.off_part);
   }
   a.segmented = L.segmented ? 1 : 0;
   if (L.segmented) {
     a.ws.stash = w.stash;
-    a.workers = std::min(a.workers, w.stash_wgs);
+    a.workers = std::min({a.workers, w.stash_wgs, a.max_items});
   }
   a.ws.err = w.err;
   rl::KernelTimer slot;
@@ -1338,51 +1335,48 @@ int rl_attn_diag_extend_plan(const int32_t* qo_indptr, const int32_t* kv_lens, i
   a.max_items = L.max_units + L.max_slots;
   const int4 none = make_int4(-1, -1, -1, -1);
   int hdr[64] = {};
-  std::vector<int4> items((size_t)a.max_items, none), munits((size_t)L.max_slots, none);
-  std::vector<int2> segs((size_t)a.max_items, make_int2(-1, -1)), mslots((size_t)L.max_slots, make_int2(-1, -1));
+  std::vector<int4> items((size_t)a.max_items, none);
+  std::vector<int2> segs((size_t)a.max_items, make_int2(-1, -1));
+  std::vector<int> arrived((size_t)L.max_slots, -1);
+  a.segmented = L.segmented ? 1 : 0;
   a.ws.hdr = hdr;
   a.ws.items = items.data();
   if (L.max_slots > 0) {
     a.ws.segs = segs.data();
-    a.ws.munits = munits.data();
-    a.ws.mslots = mslots.data();
+    a.ws.arrived = arrived.data();
   }
   int split_seqs = 0;
   const int bad = rl::plan_extend_on_host(a, &split_seqs);
-  // the units that will be finished, and of them those without all their parts in the list
-  std::vector<char> have((size_t)L.max_slots, 0);
-  int64_t listed = 0, parts = 0, broken = 0;
-  for (size_t i = 0; i < items.size(); ++i)
-    if (items[i].x >= 0) {
-      ++listed;
-      if (segs[i].y < 0) continue;
-      ++parts;
-      have[segs[i].y] = 1;
-    }
-  for (int u = 0; u < hdr[1]; ++u) {
-    const int4 it = munits[u];
-    if (it.x < 0) {
-      ++broken;
-      continue;
-    }
+  // a part's arrival counts at the slot of its unit's segment 0, as the kernel counts it
+  int64_t listed = 0, parts = 0, finished = 0, broken = 0;
+  std::vector<int> want((size_t)L.max_slots, 0);
+  for (size_t i = 0; i < items.size(); ++i) {
+    const int4 it = items[i];
+    if (it.x < 0) continue;
+    ++listed;
+    if (segs[i].x < 0) continue;
+    ++parts;
     int dummy = 0;
     const rl::SeqRange r = rl::seq_range(a, it.x, &dummy);
-    const int prefix = r.kv - r.n, nt = rl::unit_tiles(r.n, a.tile_tokens);
-    int slot = mslots[u].x + mslots[u].y;
-    bool whole = true;
-    for (int s = 0; s < rl::segment_count(prefix + it.y + it.z); ++s) {
-      whole = whole && slot >= 0 && slot < L.max_slots && have[slot];
-      slot -= rl::segment_tiles(s + 1, prefix, r.n, nt, a.tile_tokens);
+    int slot0 = segs[i].y;
+    for (int s = 1; s <= segs[i].x; ++s) slot0 = rl::slot_before(slot0, s, r.kv - r.n, r.n, a.tile_tokens);
+    if (slot0 < 0 || slot0 >= L.max_slots || arrived[slot0] < 0) {
+      ++broken;                       // (its counter was not cleared)
+      continue;
     }
-    broken += !whole;
+    ++arrived[slot0];
+    want[slot0] = rl::segment_count(r.kv - r.n + it.y + it.z);
   }
+  for (int u = 0; u < L.max_slots; ++u)
+    if (want[u] > 0) (arrived[u] == want[u] ? finished : broken) += 1;
   out[0] = listed;
   out[1] = parts;
   out[2] = split_seqs;
-  out[3] = hdr[1];
+  out[3] = finished;
   out[4] = broken;
   out[5] = bad;
   out[6] = L.max_units;
+  out[7] = hdr[1];
   return RL_OK;
 }
 

@@ -245,14 +245,18 @@ __device__ __forceinline__ void tile_attend(const PagedKV& kv, float scale, cons
 }
 
 // ---- key segments -----------------------------------------------------------
-// The extend routines (tile_attend_pp, tile_attend_dl) define a row's result
-// over more than kSegKeys keys as the merge, in key order, of one partial per
-// key segment; each partial starts from an empty state. The
+// A row of extend over more than kSegKeys keys is the merge, in key order, of
+// one partial per key segment; each partial is a run of tile_attend_pp or
+// tile_attend_dl over the segment's keys from an empty state. The
 // boundaries are fixed key positions, so the segments can be computed by one
-// workgroup after another (the running merge is kept in memory, seg_flush) or
-// by several at once (merge_segments_kernel), with the same bits: whether a
+// workgroup after another (the running merge is kept in memory, seg_merge) or
+// by several (seg_join of their partials), with the same bits: whether a
 // call splits its keys to fill the chip does not change a row. A segment in
-// which a row sees no key leaves its state untouched.
+// which a row sees no key leaves its state untouched. Each segment is a run of
+// its own, with a pipeline start of 3-5 us, so the step loops carry nothing of
+// the merge: with the boundary as a step inside the loop the 128-key kernels
+// spilled and the others took 2-3% more scalar work (multi-turn batch 41.1 ms,
+// 40.2 this way; deterministic decode of the ragged batch 1.69 and 1.62).
 
 // Running maximum of a row that has seen no key of a later segment: finite, so
 // that its step needs no test (masked scores give p = exp2(-inf) = 0 and the
@@ -280,15 +284,19 @@ __device__ __forceinline__ float seg_mix(float x0, float x1, const SegWeights& w
 }
 
 // A wave's state in memory: o as 16 float4 per lane, lane after lane (element
-// 4 i + e of chunk 4 jd + i is o[jd][4 i + e]), then m and l.
-__device__ __forceinline__ void seg_store(float* p, const f32x16 (&o)[4], float m, float l) {
+// 4 i + e of chunk 4 jd + i is o[jd][4 i + e]), then m and l. Stored and read
+// back non-temporally: the states of an XCD's 32 workgroups (4.3 MB) would
+// push the keys they share out of its 4 MB L2.
+typedef __attribute__((address_space(1))) float StateWord;
+typedef __attribute__((address_space(1))) f32x4 StateQuad;
+__device__ __forceinline__ void seg_store(StateWord* p, const f32x16 (&o)[4], float m, float l) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int jd = 0; jd < 4; ++jd)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<f32x4*>(p + 256 * (4 * jd + i) + 4 * lane) =
-          f32x4{o[jd][4 * i], o[jd][4 * i + 1], o[jd][4 * i + 2], o[jd][4 * i + 3]};
+      __builtin_nontemporal_store(f32x4{o[jd][4 * i], o[jd][4 * i + 1], o[jd][4 * i + 2], o[jd][4 * i + 3]},
+                                  (StateQuad*)(p + 256 * (4 * jd + i) + 4 * lane));
   p[4096 + lane] = m;
   p[4160 + lane] = l;
 }
@@ -296,13 +304,13 @@ __device__ __forceinline__ void seg_store(float* p, const f32x16 (&o)[4], float 
 // are loaded kSegAhead ahead of their merge (fenced: all at once they would not
 // fit the registers).
 constexpr int kSegAhead = 1;
-__device__ __forceinline__ void seg_merge(const float* p, f32x16 (&o)[4], float& m, float& l) {
+__device__ __forceinline__ void seg_merge(const StateWord* p, f32x16 (&o)[4], float& m, float& l) {
   const int lane = threadIdx.x & 63;
   f32x4 x[kSegAhead + 1][4];
   auto load = [&](int jd) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      x[jd % (kSegAhead + 1)][i] = *reinterpret_cast<const f32x4*>(p + 256 * (4 * jd + i) + 4 * lane);
+      x[jd % (kSegAhead + 1)][i] = __builtin_nontemporal_load((const StateQuad*)(p + 256 * (4 * jd + i) + 4 * lane));
   };
   const float m0 = p[4096 + lane], l0 = p[4160 + lane];
 #pragma unroll
@@ -319,23 +327,31 @@ __device__ __forceinline__ void seg_merge(const float* p, f32x16 (&o)[4], float&
     __builtin_amdgcn_sched_barrier(0);
   }
 }
-// Ends a segment inside a workgroup's run over all keys (after its last PV
-// MFMAs, before the new segment's scores need registers): its partial joins the
-// running merge at p (the first segment's becomes it), and the state restarts.
-__device__ __forceinline__ void seg_flush(float* p, bool first, f32x16 (&o)[4], float& m, float& l) {
-  // (hidden from the compiler, which would otherwise compute the addresses
-  // before the step loop and keep them in registers)
-  asm volatile("" : "+s"(p));
-  __builtin_amdgcn_sched_barrier(0);
-  if (!first) seg_merge(p, o, m, l);
-  seg_store(p, o, m, l);
-  __builtin_amdgcn_sched_barrier(0);
-  m = kNoKey;
-  l = 0.f;
+// (o, m, l) = the state at p, and (o, m, l) merged with the later segment at p.
+__device__ __forceinline__ void seg_load(const StateWord* p, f32x16 (&o)[4], float& m, float& l) {
+  const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int jd = 0; jd < 4; ++jd)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) o[jd][e] = 0.f;
+    for (int i = 0; i < 4; ++i) {
+      const f32x4 x = __builtin_nontemporal_load((const StateQuad*)(p + 256 * (4 * jd + i) + 4 * lane));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[jd][4 * i + e] = x[e];
+    }
+  m = p[4096 + lane];
+  l = p[4160 + lane];
+}
+__device__ __forceinline__ void seg_join(const StateWord* p, f32x16 (&o)[4], float& m, float& l) {
+  f32x16 x[4];
+  float m1, l1;
+  seg_load(p, x, m1, l1);
+  const SegWeights w = seg_weights(m, m1, sum_l32(l1));
+  l = seg_mix(l, l1, w);
+  m = w.m;
+#pragma unroll
+  for (int jd = 0; jd < 4; ++jd)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[jd][e] = seg_mix(o[jd][e], x[jd][e], w);
 }
 
 // The same attention with a ping-pong schedule for eight waves (two per SIMD).
@@ -355,10 +371,7 @@ __device__ __forceinline__ void seg_flush(float* p, bool first, f32x16 (&o)[4], 
 // stages its rows and meets every barrier but issues no MFMA and no softmax
 // work (the two instances keep the same barrier sequence).
 //
-// t_lo is 0 or the start of a segment. With kSeg, a run that passes segment
-// boundaries leaves the merge of all but its last segment at `stash` (this
-// wave's); the step after a boundary is an instance of its own, so the step
-// loop carries nothing of it.
+// t_lo is 0 or the start of a segment.
 //
 // kUniformPages: in-page byte offsets fit 31 bits. A wave stages four
 // consecutive key rows of each 32-row set of a step, and pages hold at least
@@ -371,10 +384,10 @@ __device__ __forceinline__ void seg_flush(float* p, bool first, f32x16 (&o)[4], 
 // sequence's final step, which stays in the page of its set. Otherwise every
 // thread looks up the page of each row it stages.
 template <int kWaves, bool kUniformPages, bool kFp8 = false, bool kCompute = true, bool kSetPages = false,
-          bool kNt = false, bool kSeg = false>
+          bool kNt = false>
 __device__ __forceinline__ void tile_attend_pp(const PagedKV& kv, float scale, const int* bt_row, int g, int t_lo,
                                                int t_hi, int t_full, int limit, const bf16x8 (&qv)[8], TileLds& lds,
-                                               f32x16 (&o)[4], float& m_run, float& l_run, int& bad, float* stash) {
+                                               f32x16 (&o)[4], float& m_run, float& l_run, int& bad) {
   static_assert(kWaves == 8, "the ping-pong schedule pairs two waves on each SIMD");
   constexpr int kAhead = 3;                       // LDS operand reads in flight ahead of the MFMAs
   const int tid = threadIdx.x;
@@ -656,24 +669,9 @@ __device__ __forceinline__ void tile_attend_pp(const PagedKV& kv, float scale, c
     next_page(j);
     __syncthreads();
   };
-  constexpr int kSegSteps = kSegKeys / kKeys;
-  // (a split unit's item starts at its segment and meets no boundary)
-  int j = 1, j_seg = kSeg && t_lo == 0 ? kSegSteps : nsteps;   // the next boundary's step
-  for (;;) {
-    const int j_end = min(nsteps, j_seg);
-    for (; j < j_end; ++j) {
-      mfma_phase(yes, yes, (j - 1) & 1, j & 1);
-      rest_of_step(j);
-    }
-    if (!kSeg || j >= nsteps) break;
-    if constexpr (kSeg) {
-      mfma_phase(yes, no, (j - 1) & 1, 0);
-      if constexpr (kCompute) seg_flush(stash, j == kSegSteps, o, m_run, l_run);
-      mfma_phase(no, yes, 0, j & 1);
-      rest_of_step(j);
-    }
-    ++j;
-    j_seg *= 2;
+  for (int j = 1; j < nsteps; ++j) {
+    mfma_phase(yes, yes, (j - 1) & 1, j & 1);
+    rest_of_step(j);
   }
   mfma_phase(yes, no, (nsteps - 1) & 1, 0);
   if (!late) __syncthreads();
@@ -717,11 +715,11 @@ constexpr int kDlVBytes = 32 * kDlVPitch;
 // phase j, by the second group at the start of its softmax phase j-1. Each
 // wave waits for its own loads before the barrier after which they are first
 // read, one MFMA phase and one softmax phase later.
-template <bool kCompute, bool kNt, bool kSeg>
+template <bool kCompute, bool kNt>
 __device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, const int* bt_row, int g, int t_lo,
                                                int t_hi, int t_full, int limit, const bf16x8 (&qv)[8], char* kl0,
                                                char* kl1, char* vl0, char* vl1, f32x16 (&o)[4], float& m_run,
-                                               float& l_run, int& bad, float* stash) {
+                                               float& l_run, int& bad) {
   constexpr int kAhead = 3;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -731,7 +729,6 @@ __device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, c
   const float sl2 = scale * kLog2e;
   if (t_lo >= t_hi) return;
   const int nsteps = (t_hi - t_lo + kDlKeys - 1) / kDlKeys;
-  constexpr int kSegSteps = kSegKeys / kDlKeys;
   const int pmask = kv.page_size - 1;
 
   // loads: wave w fills blocks w + 8 i (i = 0..3) of K and of V; block b holds
@@ -960,23 +957,17 @@ __device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, c
       barrier();
     }
     // step j: K(j) in buffer j % 2, V(j-1) in buffer (j-1) % 2
-    constexpr int kFirst = 0, kNext = 1, kFlush = 2;   // kFlush: the step after a segment boundary
-    auto body = [&](int j, auto par, auto kind) {
-      constexpr int P = decltype(par)::value, K = decltype(kind)::value;
+    auto body = [&](int j, auto par, auto first) {
+      constexpr int P = decltype(par)::value;
       char* kcur = P ? kl1 : kl0;
       char* vprev = P ? vl0 : vl1;
       auto hook = [&](int ii) {
         if constexpr (!kLate) issue_block(j, par, ii);
       };
-      if constexpr (K == kFirst) {
+      if constexpr (decltype(first)::value)
         mfma_phase(no, yes, vprev, kcur, hook);
-      } else if constexpr (K == kNext) {
+      else
         mfma_phase(yes, yes, vprev, kcur, hook);
-      } else {
-        mfma_phase(yes, no, vprev, kcur, hook);
-        if constexpr (kCompute) seg_flush(stash, j == kSegSteps, o, m_run, l_run);
-        mfma_phase(no, yes, vprev, kcur, none);
-      }
       if constexpr (!kLate) issue_done(j);
       if constexpr (kLate) wait_loads();
       barrier();
@@ -990,22 +981,13 @@ __device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, c
     };
     const std::integral_constant<int, 0> even{};
     const std::integral_constant<int, 1> odd{};
-    const std::integral_constant<int, kNext> next{};
-    body(0, even, std::integral_constant<int, kFirst>{});
-    // (a boundary's step is even: a segment is an even number of steps)
-    int j = 1, j_seg = kSeg && t_lo == 0 ? kSegSteps : nsteps;   // the next boundary's step
-    for (;;) {
-      const int j_end = min(nsteps, j_seg);
-      for (; j + 1 < j_end; j += 2) {
-        body(j, odd, next);
-        body(j + 1, even, next);
-      }
-      if (j < j_end) body(j++, odd, next);
-      if (!kSeg || j >= nsteps) break;
-      if constexpr (kSeg) body(j, even, std::integral_constant<int, kFlush>{});
-      ++j;
-      j_seg *= 2;
+    body(0, even, yes);
+    int j = 1;
+    for (; j + 1 < nsteps; j += 2) {
+      body(j, odd, no);
+      body(j + 1, even, no);
     }
+    if (j < nsteps) body(j, odd, no);
     // PV of the final step: V(n-1) in buffer (n-1) % 2
     if ((nsteps - 1) & 1)
       mfma_phase(yes, no, vl1, kl0, none);

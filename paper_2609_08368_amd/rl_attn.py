@@ -350,8 +350,8 @@ def diag_extend_plan(kv_lens, num_q_heads, num_kv_heads, max_tokens, qo_indptr=N
     ind = None if qo_indptr is None else (ctypes.c_int32 * (b + 1))(*[int(x) for x in qo_indptr])
     if total_q is None:
         total_q = b * query_tokens if qo_indptr is None else int(qo_indptr[-1])
-    out = (ctypes.c_int64 * 7)()
+    out = (ctypes.c_int64 * 8)()
     _check(lib().rl_attn_diag_extend_plan(ind, lens, b, total_q, query_tokens, num_q_heads, num_kv_heads, max_tokens,
                                           cus, out))
-    keys = ("items", "parts", "split_seqs", "split_units", "broken_units", "errors", "max_units")
+    keys = ("items", "parts", "split_seqs", "split_units", "broken_units", "errors", "max_units", "mode")
     return dict(zip(keys, (int(x) for x in out)))
