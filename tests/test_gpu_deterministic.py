@@ -177,8 +177,9 @@ def test_split_and_whole_units_give_the_same_bits(case):
     H.say(f"split against whole units {case}")
     t = (wl.materialize_fp8 if fp8 else wl.materialize)(w, DEV)
     edges = [1, 64, 4097, 16383, 16384, 16385, 16386, 16448, 16512, 32767, 32768, 32769, 33000]
-    n = max(len(edges), 4000 // hkv)              # more than four units per CU: no unit is split
+    n = min(1024, 4000 // hkv)                    # so many units that none is worth a split
     lens = (edges * -(-n // len(edges)))[:n]
+    assert split_units(lens, hq, hkv, t["block_table"].shape[1] * ps) == 0
     g = torch.Generator(device=DEV)
     g.manual_seed(7)
     many = dict(t, q=torch.randn((n, hq, 128), generator=g, device=DEV).to(torch.bfloat16),
@@ -186,6 +187,7 @@ def test_split_and_whole_units_give_the_same_bits(case):
                 kv_lens=torch.tensor(lens, dtype=torch.int32, device=DEV))
     full_o, full_l = det_decode(many, fp8=fp8)
     for rows in ([len(edges) - 1], [4, 5, 6], list(range(len(edges)))):
+        assert split_units([lens[i] for i in rows], hq, hkv, t["block_table"].shape[1] * ps) > 0
         o, l = det_decode(many, rows=rows, fp8=fp8)
         idx = torch.tensor(rows, device=DEV)
         assert bits_equal(o, full_o[idx]), f"rows {rows}: split keys change the bits"
@@ -197,6 +199,112 @@ def test_split_and_whole_units_give_the_same_bits(case):
     ref = call(many["q"][sel].contiguous(), *args, many["block_table"][sel].contiguous(),
                many["kv_lens"][sel].contiguous(), t["scale"], lse=lse)
     H.compare(full_o[sel], H.f64(ref), max_abs=2e-2, rel_rms=5e-3, what="segments vs split-KV decode")
+
+
+def split_units(lens, hq, hkv, room, indptr=None):
+    """Units whose keys the planner gives to several workgroups (decode rows, or chunks of ``indptr``)."""
+    plan = ra.diag_extend_plan([int(x) for x in lens], hq, hkv, room, qo_indptr=indptr,
+                               query_tokens=0 if indptr is not None else 1,
+                               cus=torch.cuda.get_device_properties(0).multi_processor_count)
+    assert plan["errors"] == 0 and plan["broken_units"] == 0
+    return plan["split_units"]
+
+
+@pytest.mark.parametrize("case", [(16, False), (64, False), (64, True), (8, True)],
+                         ids=["P16_bf16", "P64_bf16", "P64_fp8", "P8_fp8"])
+def test_chunks_across_boundaries_whole_split_and_token_by_token(case):
+    """Chunks of several tiles with rows on both sides of a segment boundary (16384 and 32768): in a
+    batch whose units stay whole, alone with the keys split, and one token at a time.
+    In the first two a row before the boundary sees no key of a segment its unit runs."""
+    ps, fp8 = case
+    hq, hkv, n, B = 16, 2, 150, 112
+    base = wl.custom(160 + ps, "extend", [33200], q_lens=[n], hq=hq, hkv=hkv, page_size=ps)
+    H.say(f"chunks across boundaries {case}")
+    t = (wl.materialize_fp8 if fp8 else wl.materialize)(base, DEV)
+    edges = [16384 + 90, 32768 + 60, 33200, 16384 + 149, 32768 + 1, 16384, 16385]
+    lens = (edges * -(-B // len(edges)))[:B]
+    indptr = np.arange(B + 1) * n
+    g = torch.Generator(device=DEV)
+    g.manual_seed(11)
+    one = t["block_table"][0:1]
+    many = dict(t, q=torch.randn((B * n, hq, 128), generator=g, device=DEV).to(torch.bfloat16),
+                block_table=one.expand(B, -1).contiguous(),
+                kv_lens=torch.tensor(lens, dtype=torch.int32, device=DEV),
+                qo_indptr=torch.tensor(indptr, dtype=torch.int32, device=DEV))
+    assert split_units(lens, hq, hkv, t["block_table"].shape[1] * ps, indptr) == 0
+    whole_o, whole_l = H.run_extend(None, many)
+    for b in range(len(edges)):
+        rows = slice(b * n, (b + 1) * n)
+        alone = dict(many, q=many["q"][rows].contiguous(), block_table=one.contiguous(),
+                     kv_lens=many["kv_lens"][b:b + 1].contiguous(),
+                     qo_indptr=torch.tensor([0, n], dtype=torch.int32, device=DEV))
+        assert (split_units([lens[b]], hq, hkv, t["block_table"].shape[1] * ps, [0, n]) > 0) == (lens[b] > 16384)
+        o, l = H.run_extend(None, alone)
+        assert bits_equal(o, whole_o[rows]) and bits_equal(l, whole_l[rows]), f"kv {lens[b]}: split keys change the bits"
+        step = dict(many, q=alone["q"], block_table=one.expand(n, -1).contiguous(),
+                    kv_lens=torch.arange(lens[b] - n + 1, lens[b] + 1, dtype=torch.int32, device=DEV))
+        o, l = det_decode(step, fp8=fp8)
+        assert bits_equal(o, whole_o[rows]) and bits_equal(l, whole_l[rows]), f"kv {lens[b]}: token by token differs"
+    step = dict(many, q=many["q"][:n].contiguous(), block_table=one.expand(n, -1).contiguous(),
+                kv_lens=torch.arange(lens[0] - n + 1, lens[0] + 1, dtype=torch.int32, device=DEV))
+    call = ra.decode_fp8 if fp8 else ra.decode
+    pages = (t["k_pages"], t["v_pages"]) + ((t["k_scale"], t["v_scale"]) if fp8 else ())
+    ref = call(step["q"], *pages, step["block_table"], step["kv_lens"], t["scale"])
+    H.compare(whole_o[:n], H.f64(ref), max_abs=2e-2, rel_rms=5e-3, what="chunk vs split-KV decode")
+
+
+@pytest.mark.parametrize("case", [(64, False), (16, False), (64, True)], ids=["P64_bf16", "P16_bf16", "P64_fp8"])
+def test_table_width_does_not_change_the_bits(case):
+    """The same rows behind a table as wide as the longest of them (one segment) and behind one of
+    64K tokens, alone and beside a long row (which makes every unit run by segments)."""
+    ps, fp8 = case
+    hq, hkv = 24, 2
+    lens, n = [1, 300, 4097, 9000, 16384], [1, 40, 130, 1, 70]
+    w = wl.custom(170 + ps, "extend", lens + [20000], q_lens=n + [33], hq=hq, hkv=hkv, page_size=ps)
+    H.say(f"table width {case}")
+    t = (wl.materialize_fp8 if fp8 else wl.materialize)(w, DEV)
+    exact = 16384 // ps
+    wide = torch.full((w.batch, 65536 // ps), -1, dtype=torch.int32, device=DEV)   # (never read behind a row's keys)
+    wide[:, :t["block_table"].shape[1]] = t["block_table"]
+    rows, B = sum(n), len(lens)
+    tables = {"exact": t["block_table"][:B, :exact].contiguous(), "wide": wide[:B].contiguous(), "beside a long row": wide}
+    got, got_d = {}, {}
+    for name, bt in tables.items():
+        k = bt.shape[0]
+        m = int(t["qo_indptr"][k])
+        call = dict(t, q=t["q"][:m].contiguous(), block_table=bt, kv_lens=t["kv_lens"][:k].contiguous(),
+                    qo_indptr=t["qo_indptr"][:k + 1].contiguous())
+        plan = ra.diag_extend_plan((lens + [20000])[:k], hq, hkv, bt.shape[1] * ps, qo_indptr=w.qo_indptr[:k + 1])
+        assert (plan["mode"] > 0) == (k > B)
+        o, l = H.run_extend(None, call)
+        got[name] = (o[:rows].clone(), l[:rows].clone())
+        o, l = det_decode(dict(call, q=t["q"][:k].contiguous()), fp8=fp8)
+        got_d[name] = (o[:B].clone(), l[:B].clone())
+    for d in (got, got_d):
+        for name in ("wide", "beside a long row"):
+            assert bits_equal(d["exact"][0], d[name][0]) and bits_equal(d["exact"][1], d[name][1]), name
+    ra.check_device_errors()
+
+
+def test_split_units_repeat_exactly():
+    """Parts of a unit arrive in any order from any XCD: the rows are the same every time, also right
+    after a call that left other partials in the same slots."""
+    hq, hkv, ps = 32, 8, 64
+    w = wl.custom(181, "decode", [40000, 17000, 33000, 16385, 20000, 65000], hq=hq, hkv=hkv, page_size=ps)
+    H.say("split units, repeated")
+    t = wl.materialize(w, DEV)
+    assert split_units(w.kv_lens, hq, hkv, t["block_table"].shape[1] * ps) == 6 * hkv
+    first, lse = det_decode(t)
+    other = dict(t, q=-t["q"])
+    for rep in range(60):
+        out, l = torch.empty_like(first), torch.empty_like(lse)
+        ra.decode(other["q"], t["k_pages"], t["v_pages"], t["block_table"], t["kv_lens"], t["scale"], out=out, lse=l,
+                  deterministic=True)
+        ra.decode(t["q"], t["k_pages"], t["v_pages"], t["block_table"], t["kv_lens"], t["scale"], out=out, lse=l,
+                  deterministic=True)
+        assert bits_equal(out, first) and bits_equal(l, lse), f"repeat {rep}"
+    ref_o, ref_l = H.oracle_full(w, t)
+    H.compare(first, ref_o, lse, ref_l, what="split units")
 
 
 @pytest.mark.parametrize("ps", [16, 64])

@@ -2,12 +2,15 @@
 a very long single sequence (hundreds of thousands of keys, a block-table row of
 thousands of pages), a 128-wide GQA group (128 query heads on one KV head),
 the most query tokens per sequence a multi-token decode takes (64), a whole
-prompt prefilled as one chunk, and batches of thousands of sequences.
+prompt prefilled as one chunk, batches of thousands of sequences, and chunks that
+overlap (an invalid qo_indptr) behind long prefixes.
 """
 
 import numpy as np
 import pytest
+import torch
 
+from paper_2609_08368_amd import rl_attn as ra
 from paper_2609_08368_amd import workloads as wl
 from tests import gpu_helpers as H
 from tests.test_gpu_mtp import check as mtp_check
@@ -102,3 +105,31 @@ def test_decode_large_batch(deterministic):
     out, lse = H.run_decode(w, t, deterministic=deterministic)
     ref_o, ref_l = H.oracle_full(w, t)
     H.compare(out, ref_o, lse, ref_l, what=f"decode B=3000 det={deterministic}")
+
+
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+def test_overlapping_chunks_behind_long_prefixes_stay_in_their_buffers(fp8):
+    """A qo_indptr that runs back ([0, 256, 0, 256, ...]) makes chunks overlap: more units behind 20,000
+    keys each than the call's rows allow for. The call is reported, rows outside
+    out and lse stay as they were, and the next valid call is right."""
+    n, B = 256, 14
+    w = wl.custom(309, "extend", [20000], q_lens=[n], hq=64, hkv=8, page_size=64)
+    H.say(f"overlapping chunks fp8={fp8}")
+    t = (wl.materialize_fp8 if fp8 else wl.materialize)(w, DEV)
+    pages = (t["k_pages"], t["v_pages"]) + ((t["k_scale"], t["v_scale"]) if fp8 else ())
+    call = ra.extend_fp8 if fp8 else ra.extend
+    out_all = torch.full((3 * n, 64, 128), 7.0, dtype=torch.bfloat16, device=DEV)
+    lse_all = torch.full((3 * n, 64), 7.0, dtype=torch.float32, device=DEV)
+    indptr = torch.tensor([0, n] * (B // 2) + [0], dtype=torch.int32, device=DEV)
+    ra.check_device_errors()
+    call(t["q"], indptr, *pages, t["block_table"].expand(B, -1).contiguous(),
+         torch.full((B,), 20000, dtype=torch.int32, device=DEV), t["scale"], out=out_all[n:2 * n], lse=lse_all[n:2 * n])
+    with pytest.raises(ra.RlAttnError, match="qo_indptr-invalid"):
+        ra.check_device_errors()
+    for part in (out_all[:n], out_all[2 * n:], lse_all[:n], lse_all[2 * n:]):
+        assert bool((part == 7).all())
+    out, lse = H.run_extend(w, t)
+    ra.check_device_errors()
+    ref = ra.decode_fp8 if fp8 else ra.decode
+    last = ref(t["q"][n - 1:].contiguous(), *pages, t["block_table"], t["kv_lens"], t["scale"])
+    H.compare(out[n - 1:], H.f64(last), what="the next call's last row against decode")
