@@ -195,6 +195,8 @@ __device__ __forceinline__ UnitRow unit_row(const ExtendArgs& a, int r, int cnt,
 
 // Joins a split unit's partials in key order, as a workgroup that has all of the
 // unit's segments does (row block `wave` of the unit). slot0: the slot of segment 0.
+// (The slots follow from the lengths, which are read again here: a caller that
+// changes them under a running call gets wrong rows, but no slot outside the buffer.)
 __device__ __forceinline__ void join_parts(const ExtendArgs& a, int slot0, int n_seg, int prefix, int n, int wave,
                                            f32x16 (&o)[4], float& m, float& l) {
   int slot = slot0;
@@ -204,8 +206,16 @@ __device__ __forceinline__ void join_parts(const ExtendArgs& a, int slot0, int n
       seg_load(p, o, m, l);
     else
       seg_join(p, o, m, l);
-    if (s + 1 < n_seg) slot -= segment_tiles(s + 1, prefix, n, unit_tiles(n, a.tile_tokens), a.tile_tokens);
+    if (s + 1 < n_seg) slot = max(0, slot - segment_tiles(s + 1, prefix, n, unit_tiles(n, a.tile_tokens), a.tile_tokens));
   }
+}
+
+// The kernel's arguments, read again (the empty asm hides that they are the same).
+__device__ __forceinline__ ExtendArgs reread_args() {
+  typedef __attribute__((address_space(4))) const ExtendArgs ConstArgs;
+  ConstArgs* ap = (ConstArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(ap));
+  return *(const ExtendArgs*)ap;
 }
 
 // The LDS of a workgroup. The K and V buffers of the 128-key steps are arrays of
@@ -230,10 +240,9 @@ __device__ __forceinline__ void extend_unit(const ExtendArgs& a, int unit, const
   const int prefix = sr.kv - sr.n;
   const int t_unit = prefix + i0 + cnt;    // keys [0, t_unit) are visible to some row
   const int t_full = prefix + i0;          // keys [0, t_full) are visible to every row
-  // segments [seg, seg_end) of the unit's n_seg: one of a split unit, else all
+  // segments of the unit's n_seg: one of a split unit, else all in turn
   const int n_seg = kSeg ? segment_count(t_unit) : 1;
   int seg = part.x >= 0 ? part.x : 0;
-  const int seg_end = part.x >= 0 ? part.x + 1 : n_seg;
 
   const UnitRow row = unit_row(a, wave * kWaveRows + (lane & 31), cnt, g, hb);
   const int limit = row.ok ? prefix + i0 + row.ti : t_unit - 1;
@@ -250,47 +259,63 @@ __device__ __forceinline__ void extend_unit(const ExtendArgs& a, int unit, const
   // the one token of a deterministic decode) only stages
   const bool active = __builtin_amdgcn_ballot_w64(row.ok) != 0;
   f32x16 o[4];
-  float m_run, l_run;
+  float m_run = kNegInf, l_run = 0.f;
+  const bool whole = kSeg && part.x < 0 && n_seg > 1;   // this workgroup merges the unit's segments
   for (;;) {
     const int t_lo = segment_start(seg);
     const int t_end = seg + 1 < n_seg ? segment_start(seg + 1) : t_unit;
+    // the segment before joins the running merge while this one's first rows are
+    // on their way (its address is hidden from the compiler, which would otherwise
+    // form it before the segments and spill: 133 instead of 115 us for 128 x 1K rows)
+    auto begin = [&]() {
+      if (kSeg && whole && seg > 0) {
+        const ExtendArgs e = reread_args();
+        StateWord* stash = (StateWord*)e.ws.stash + ((size_t)blockIdx.x * e.slot_waves + swave) * kSegWaveFloats;
+        asm volatile("" : "+s"(stash));
+        if (seg > 1) seg_merge(stash, o, m_run, l_run);
+        seg_store(stash, o, m_run, l_run);
+      }
 #pragma unroll
-    for (int jd = 0; jd < 4; ++jd)
+      for (int jd = 0; jd < 4; ++jd)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) o[jd][e] = 0.f;
-    m_run = kSeg && seg > 0 ? kNoKey : kNegInf;
-    l_run = 0.f;
-    auto attend = [&](auto compute_tag) {
+        for (int e = 0; e < 16; ++e) o[jd][e] = 0.f;
+      m_run = kSeg && seg > 0 ? kNoKey : kNegInf;
+      l_run = 0.f;
+    };
+    auto attend = [&](auto compute_tag, auto&& start) {
       constexpr bool kC = decltype(compute_tag)::value;
       if constexpr (kPages == kDirectPages) {
         static_assert(!kFp8, "rows go to LDS as stored: bf16 pages only");
         tile_attend_dl<kC, kNt>(a.kv, scale, bt_row, g, t_lo, t_end, t_full, limit, qv, lds.kl0, lds.kl1, lds.vl0,
-                                lds.vl1, o, m_run, l_run, bad);
+                                lds.vl1, o, m_run, l_run, bad, start);
       } else {
         tile_attend_pp<kExtWaves, kPages != kRowPages, kFp8, kC, kPages == kSetPages, kNt>(
-            a.kv, scale, bt_row, g, t_lo, t_end, t_full, limit, qv, *lds, o, m_run, l_run, bad);
+            a.kv, scale, bt_row, g, t_lo, t_end, t_full, limit, qv, *lds, o, m_run, l_run, bad, start);
       }
     };
+    // (pages of fewer than 64 keys: before the rows, 6344 against 6442 us for twelve
+    // turns of 512-1024 tokens behind 20-30K keys)
+    constexpr bool kBefore = kPages == kSetPages;
+    if (kBefore && active) begin();
     if (active)
-      attend(std::true_type{});
+      attend(std::true_type{}, [&] {
+        if constexpr (!kBefore) begin();
+      });
     else
-      attend(std::false_type{});
+      attend(std::false_type{}, [] {});
     if constexpr (!kSeg) break;
-    if (part.x >= 0 || n_seg == 1) break;
-    // all segments of the unit are this workgroup's: they join the running
-    // merge (its address is hidden from the compiler, which would otherwise form
-    // it before the segments and spill: 133 instead of 115 us for 128 x 1K rows)
-    StateWord* stash = (StateWord*)a.ws.stash + ((size_t)blockIdx.x * a.slot_waves + swave) * kSegWaveFloats;
-    asm volatile("" : "+s"(stash));
-    if (active) {
-      if (seg > 0) seg_merge(stash, o, m_run, l_run);
-      if (seg + 1 < seg_end) seg_store(stash, o, m_run, l_run);
-    }
-    if (++seg == seg_end) break;
+    if (!whole || ++seg == n_seg) break;
     __syncthreads();                       // the LDS tiles are free
   }
+  // (as for the next unit, so that the step loop carries nothing of what follows it)
+  const ExtendArgs e = kSeg ? reread_args() : a;
+  if (kSeg && whole && active) {
+    StateWord* stash = (StateWord*)e.ws.stash + ((size_t)blockIdx.x * e.slot_waves + swave) * kSegWaveFloats;
+    asm volatile("" : "+s"(stash));
+    seg_merge(stash, o, m_run, l_run);
+  }
   // the next unit is taken only now, so that no worker holds one it cannot start
-  if (kSeg && threadIdx.x == 0) *next_unit = take_unit(a.ws.hdr + 8, n_units);
+  if (kSeg && threadIdx.x == 0) *next_unit = take_unit(e.ws.hdr + 8, n_units);
 
   bool finish = true;
   if (kSeg && part.x >= 0) {
@@ -301,37 +326,38 @@ __device__ __forceinline__ void extend_unit(const ExtendArgs& a, int unit, const
     // takes in the others' (a release by each wave cost 7% on the ragged
     // deterministic decode: it writes the XCD's L2 back).
     int slot0 = part.y;
-    for (int s = 1; s <= part.x; ++s) slot0 = slot_before(slot0, s, prefix, sr.n, a.tile_tokens);
-    StateWord* mine = (StateWord*)a.ws.part + ((size_t)part.y * a.slot_waves + swave) * kSegWaveFloats;
+    for (int s = 1; s <= part.x; ++s) slot0 = slot_before(slot0, s, prefix, sr.n, e.tile_tokens);
+    slot0 = min(slot0, e.max_slots - 1);
+    StateWord* mine = (StateWord*)e.ws.part + ((size_t)part.y * e.slot_waves + swave) * kSegWaveFloats;
     asm volatile("" : "+s"(mine));         // (as the stash's)
     if (active) seg_store(mine, o, m_run, l_run);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      const int n = __hip_atomic_fetch_add(&a.ws.arrived[slot0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+      const int n = __hip_atomic_fetch_add(&e.ws.arrived[slot0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
       if (n == n_seg) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       *parts_here = n;
     }
     __syncthreads();
     finish = __builtin_amdgcn_readfirstlane(*parts_here) == n_seg;
-    if (finish && active) join_parts(a, slot0, n_seg, prefix, sr.n, swave, o, m_run, l_run);
+    if (finish && active) join_parts(e, slot0, n_seg, prefix, sr.n, swave, o, m_run, l_run);
   }
   if (finish) {
     const float l_tot = sum_l32(l_run);
     if (row.ok) {
       const float inv = l_tot > 0.f ? dq.v / l_tot : 0.f;
-      if (a.out_f32)
-        store_o_row((float*)a.out + qrow * a.out_st + (int64_t)row.head * a.out_sh, o, inv);
+      if (e.out_f32)
+        store_o_row((float*)e.out + qrow * e.out_st + (int64_t)row.head * e.out_sh, o, inv);
       else
-        store_o_row((__bf16*)a.out + qrow * a.out_st + (int64_t)row.head * a.out_sh, o, inv);
-      if (a.lse && lane < 32)
-        a.lse[qrow * a.lse_st + (int64_t)row.head * a.lse_sh] =
+        store_o_row((__bf16*)e.out + qrow * e.out_st + (int64_t)row.head * e.out_sh, o, inv);
+      if (e.lse && lane < 32)
+        e.lse[qrow * e.lse_st + (int64_t)row.head * e.lse_sh] =
             l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : kNegInf;
     }
   }
-  if (bad) atomicOr(a.ws.err, kErrPage);
-  if (bad_scale) atomicOr(a.ws.err, kErrScale);
+  if (bad) atomicOr(e.ws.err, kErrPage);
+  if (bad_scale) atomicOr(e.ws.err, kErrScale);
 }
 
 // Units run in list order (longest key range first). Workgroups are handed
@@ -361,13 +387,9 @@ __global__ __launch_bounds__(kExtWaves * 64, 2) void extend_mfma_kernel(ExtendAr
       if (unit >= args.workers) return;
       // every pass takes a new entry of a finite list, so the loop ends
       while (unit < n_units) {
-        // The arguments are read again for each unit (the empty asm hides that
-        // they are the same): kept over the loop they would not fit the scalar
-        // registers beside a unit's own values.
-        typedef __attribute__((address_space(4))) const ExtendArgs ConstArgs;
-        ConstArgs* ap = (ConstArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-        asm volatile("" : "+s"(ap));
-        const ExtendArgs a = *(const ExtendArgs*)ap;
+        // The arguments are read again for each unit: kept over the loop they would
+        // not fit the scalar registers beside a unit's own values.
+        const ExtendArgs a = reread_args();
         extend_unit<kFp8, kPages, kNt, true>(a, unit, it, mode, n_units, lds, &next_unit, &parts_here);
         // the LDS tiles are free and next_unit is written; it is read before the
         // next unit's barriers, which every wave passes before the next write

@@ -179,14 +179,19 @@ std::map<int, int> g_cus;
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-int device_cus(int dev) {
-  std::lock_guard<std::mutex> lk(g_mu);
+// (g_mu held)
+int device_cus_locked(int dev) {
   auto it = g_cus.find(dev);
   if (it != g_cus.end()) return it->second;
   int n = 0;
   if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
   g_cus[dev] = n;
   return n;
+}
+
+int device_cus(int dev) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  return device_cus_locked(dev);
 }
 
 // running merges of one workgroup per compute unit (units of eight waves)
@@ -199,7 +204,6 @@ int acquire_ws(hipStream_t st, size_t need, size_t want, bool need_stash, Worksp
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-  const size_t stash = stash_bytes(device_cus(dev));
   std::lock_guard<std::mutex> lk(g_mu);
   Workspace& w = g_ws[{dev, st}];
   const bool need_err = w.err == nullptr;
@@ -238,6 +242,7 @@ int acquire_ws(hipStream_t st, size_t need, size_t want, bool need_stash, Worksp
       w.size = 0;
     }
     // what the call would like, what it needs, and that without the running merges' room
+    const size_t stash = stash_bytes(device_cus_locked(dev));
     void* p = nullptr;
     size_t size = want < w.refused ? want : need, off = 0;
     for (int t = size == need ? 1 : 0;; ++t) {

@@ -371,7 +371,10 @@ __device__ __forceinline__ void seg_join(const StateWord* p, f32x16 (&o)[4], flo
 // stages its rows and meets every barrier but issues no MFMA and no softmax
 // work (the two instances keep the same barrier sequence).
 //
-// t_lo is 0 or the start of a segment.
+// t_lo is 0 or the start of a segment. begin() runs once the first rows are
+// requested and before anything else: it leaves the empty state in o, m_run and
+// l_run, and what it does with the state of a segment before costs little more
+// than those rows' latency.
 //
 // kUniformPages: in-page byte offsets fit 31 bits. A wave stages four
 // consecutive key rows of each 32-row set of a step, and pages hold at least
@@ -384,10 +387,10 @@ __device__ __forceinline__ void seg_join(const StateWord* p, f32x16 (&o)[4], flo
 // sequence's final step, which stays in the page of its set. Otherwise every
 // thread looks up the page of each row it stages.
 template <int kWaves, bool kUniformPages, bool kFp8 = false, bool kCompute = true, bool kSetPages = false,
-          bool kNt = false>
+          bool kNt = false, typename Begin>
 __device__ __forceinline__ void tile_attend_pp(const PagedKV& kv, float scale, const int* bt_row, int g, int t_lo,
                                                int t_hi, int t_full, int limit, const bf16x8 (&qv)[8], TileLds& lds,
-                                               f32x16 (&o)[4], float& m_run, float& l_run, int& bad) {
+                                               f32x16 (&o)[4], float& m_run, float& l_run, int& bad, Begin&& begin) {
   static_assert(kWaves == 8, "the ping-pong schedule pairs two waves on each SIMD");
   constexpr int kAhead = 3;                       // LDS operand reads in flight ahead of the MFMAs
   const int tid = threadIdx.x;
@@ -488,21 +491,23 @@ __device__ __forceinline__ void tile_attend_pp(const PagedKV& kv, float scale, c
       p[i] = pg;
     }
   };
-  auto fetch_u = [&](int t0, const Pids& p, const char* base, int64_t sp, uint32_t ss,
+  auto fetch_u = [&](int t0, const Pids& p, const char* base, uint32_t sp, uint32_t ss,
                      const uint32_t (&off)[kStageRows], Rows& r) {
     const int tc = t0 < t_last ? t0 : t_last;
     const uint32_t step_off = ES * ((uint32_t)(tc & pmask) * ss);   // zero when a page holds at most a step
+    // (page stride below 2^32: one scalar multiply, shared by both branches)
+    const char* page[kStageRows];
+#pragma unroll
+    for (int i = 0; i < kStageRows; ++i) page[i] = base + ES * ((uint64_t)(uint32_t)p[i] * sp);
     if (tc + kKeys <= t_hi) {
 #pragma unroll
-      for (int i = 0; i < kStageRows; ++i)
-        r[i] = load_row(base + ES * ((int64_t)p[i] * sp) + step_off + off[i]);
+      for (int i = 0; i < kStageRows; ++i) r[i] = load_row(page[i] + step_off + off[i]);
     } else {
       const int last = t_hi - 1 - tc;
 #pragma unroll
       for (int i = 0; i < kStageRows; ++i) {
         const int rr = min(ld_row + kRowStep * i, last);
-        r[i] = load_row(base + ES * ((int64_t)p[i] * sp) +
-                                 ES * (ld_chunk + ((uint32_t)(tc + rr) & (uint32_t)pmask) * ss));
+        r[i] = load_row(page[i] + ES * (ld_chunk + ((uint32_t)(tc + rr) & (uint32_t)pmask) * ss));
       }
     }
   };
@@ -597,22 +602,37 @@ __device__ __forceinline__ void tile_attend_pp(const PagedKV& kv, float scale, c
   // unconditional, so no register copy has to wait for them.
   // Invariant at the top of step j: kr = rows of K(j+1), vr = rows of V(j);
   // ids (or scalar page ids) of steps j+1 and j+2 are at hand.
-  Rows kr, vr;
+  Rows k0, kr, vr;
   Ids id_k, id_v;
   Pids pid_1 = {}, pid_2 = {};
   if constexpr (kUniformPages) {
     Pids p0;
     page_ids(t_lo, p0);
-    fetch_u(t_lo, p0, kbase_u, kv.sp, kss, koff, kr);
-    fetch_u(t_lo, p0, vbase_u, kv.v_sp, vss, voff, vr);
-    put_k(0, kr);
-    page_ids(t_lo + kKeys, pid_1);
-    fetch_u(t_lo + kKeys, pid_1, kbase_u, kv.sp, kss, koff, kr);
-    page_ids(t_lo + 2 * kKeys, pid_2);
+    // (pages of fewer than 64 keys: the first two steps' rows at once, whose page
+    // ids take a scalar load each; 0.5-1% on calls of 50-200 us, and none with
+    // one page a step)
+    if constexpr (kSetPages) {
+      page_ids(t_lo + kKeys, pid_1);
+      fetch_u(t_lo, p0, kbase_u, ksp, kss, koff, k0);
+      fetch_u(t_lo, p0, vbase_u, vsp, vss, voff, vr);
+      fetch_u(t_lo + kKeys, pid_1, kbase_u, ksp, kss, koff, kr);
+      page_ids(t_lo + 2 * kKeys, pid_2);
+      begin();
+      put_k(0, k0);
+    } else {
+      fetch_u(t_lo, p0, kbase_u, ksp, kss, koff, kr);
+      fetch_u(t_lo, p0, vbase_u, vsp, vss, voff, vr);
+      begin();
+      put_k(0, kr);
+      page_ids(t_lo + kKeys, pid_1);
+      fetch_u(t_lo + kKeys, pid_1, kbase_u, ksp, kss, koff, kr);
+      page_ids(t_lo + 2 * kKeys, pid_2);
+    }
   } else {
     load_ids(t_lo, id_k);
     fetch(t_lo, id_k, kbase, ksp, kss, kr);
     fetch(t_lo, id_k, vbase, vsp, vss, vr);
+    begin();
     put_k(0, kr);
     load_ids(t_lo + kKeys, id_v);
     fetch(t_lo + kKeys, id_v, kbase, ksp, kss, kr);
@@ -630,8 +650,8 @@ __device__ __forceinline__ void tile_attend_pp(const PagedKV& kv, float scale, c
   auto fetch_next = [&](int j) {
     const int t0 = t_lo + j * kKeys;
     if constexpr (kUniformPages) {
-      fetch_u(t0 + kKeys, pid_1, vbase_u, kv.v_sp, vss, voff, vr);
-      fetch_u(t0 + 2 * kKeys, pid_2, kbase_u, kv.sp, kss, koff, kr);
+      fetch_u(t0 + kKeys, pid_1, vbase_u, vsp, vss, voff, vr);
+      fetch_u(t0 + 2 * kKeys, pid_2, kbase_u, ksp, kss, koff, kr);
 #pragma unroll
       for (int i = 0; i < kStageRows; ++i) pid_1[i] = pid_2[i];
     } else {
@@ -715,11 +735,11 @@ constexpr int kDlVBytes = 32 * kDlVPitch;
 // phase j, by the second group at the start of its softmax phase j-1. Each
 // wave waits for its own loads before the barrier after which they are first
 // read, one MFMA phase and one softmax phase later.
-template <bool kCompute, bool kNt>
+template <bool kCompute, bool kNt, typename Begin>
 __device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, const int* bt_row, int g, int t_lo,
                                                int t_hi, int t_full, int limit, const bf16x8 (&qv)[8], char* kl0,
                                                char* kl1, char* vl0, char* vl1, f32x16 (&o)[4], float& m_run,
-                                               float& l_run, int& bad) {
+                                               float& l_run, int& bad, Begin&& begin) {
   constexpr int kAhead = 3;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -920,6 +940,7 @@ __device__ __forceinline__ void tile_attend_dl(const PagedKV& kv, float scale, c
   int pid_next = 2;                                  // step whose ids the next read fetches
   page_pair(0, pv);
   dma(0, pv, kbase, kv.sp, kss, kl0, kDlKPitch);
+  begin();
   if (nsteps > 1) page_pair(1, pk);
   wait_loads();
   barrier();
