@@ -338,7 +338,7 @@ def summarize_pmc(fetch_dir: str, write_dir: str, fp8: bool = False, extend: boo
     w = wl.decode_ragged()
     algo = w.kv_bytes() // 2 if fp8 else w.kv_bytes()
     res = {
-        "kernel": "decode_mfma_kernel<true>" if fp8 else "decode_mfma_kernel<false>",
+        "kernel": "decode_mfma_kernel<true, 1>" if fp8 else "decode_mfma_kernel<false, 1>",
         "workload": "ragged 64K decode batch (B128, Hq96/Hkv8, page 64)" + (", FP8 E4M3 pages" if fp8 else ", bf16 pages"),
         "source_hash": kernel_source_hash(),
         "fetch_kib_per_dispatch": fetch["decode"], "write_kib_per_dispatch": write["decode"],
@@ -408,7 +408,7 @@ def summarize_extend_pmc(fetch: dict, write: dict, fetch_dir: str, write_dir: st
     rd = fetch["decode"] * 1024.0 * f_scale
     wr = write["decode"] * 1024.0 * w_scale
     q_bytes = w.total_q * w.hq * 128 * 2
-    res = {"kernel": "extend_mfma_kernel<false, 0>", "workload": "multi-turn extend batch (B32, Hq64/Hkv8, page 64)",
+    res = {"kernel": "extend_mfma_kernel<false, 3, false>", "workload": "multi-turn extend batch (B32, Hq64/Hkv8, page 64)",
            "source_hash": kernel_source_hash(), "fetch_kib_per_dispatch": fetch["decode"],
            "write_kib_per_dispatch": write["decode"], "copy_fetch_kib": fetch["copy"], "copy_write_kib": write["copy"],
            "fetch_scale": f_scale, "write_scale": w_scale, "hbm_read_bytes": rd, "hbm_write_bytes": wr,
@@ -437,10 +437,12 @@ calibrate the counters (FETCH_SIZE scale {f_scale:.3f}, WRITE_SIZE scale {w_scal
 | FETCH_SIZE | {fetch['decode']:,.0f} | {rd:,.0f} | {res['read_over_kv_plus_q']:.3f} x (KV + q) |
 | WRITE_SIZE | {write['decode']:,.0f} | {wr:,.0f} | {res['write_over_out']:.3f} x out |
 
-The kernel is bound by the matrix cores, not by HBM: at about 42 ms per launch these bytes move
-at about {(rd + wr) / 42e-3 / 1e9:,.0f} GB/s. The work units of one (sequence, KV head) run
+The kernel is bound by the matrix cores, not by HBM: at about 40 ms per launch these bytes move
+at about {(rd + wr) / 40e-3 / 1e9:,.0f} GB/s. The work units of one (sequence, KV head) run
 on one XCD and share their keys through its L2, so the keys beyond the first unit's reads
-mostly come from L2. Sources hash {res['source_hash']}.
+mostly come from L2. Writes beyond out, and their reads, are the states that units of rows over
+several key segments keep at each boundary (135 KB a unit, non-temporal). Sources hash
+{res['source_hash']}.
 """)
     print(json.dumps(res, indent=1))
 

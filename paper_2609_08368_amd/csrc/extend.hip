@@ -171,7 +171,8 @@ constexpr int kStepPages = 0, kSetPages = 1, kRowPages = 2, kDirectPages = 3;
 
 // The next unit of a worker: the head of its XCD's list (entries i with
 // i % 8 == the workgroup's index % 8), or of another list once that is empty;
-// n or more when all are.
+// n or more when all are. (The XCDs do not end together: with its own list only,
+// twelve FP8 turns behind 20-30K keys took 6618 against 6154 us.)
 __device__ __forceinline__ int take_unit(int* taken, int n) {
   for (int d = 0; d < kXcds; ++d) {
     const int q = (blockIdx.x + d) & (kXcds - 1);
@@ -321,10 +322,10 @@ __device__ __forceinline__ void extend_unit(const ExtendArgs& a, int unit, const
   if (kSeg && part.x >= 0) {
     // A part of a split unit goes to its slot, and the workgroup that brings
     // the last one finishes the rows; none waits, and a unit that lacks a part
-    // is left unwritten. Once the barrier has seen every wave's stores
-    // complete, one thread makes them visible to the device, counts, and for the last part
-    // takes in the others' (a release by each wave cost 7% on the ragged
-    // deterministic decode: it writes the XCD's L2 back).
+    // is left unwritten. Every wave waits for its stores before the barrier;
+    // behind it one thread makes them visible to the device, counts, and for
+    // the last part takes in the others' (a release by each wave cost 7% on the
+    // ragged deterministic decode: it writes the XCD's L2 back).
     int slot0 = part.y;
     for (int s = 1; s <= part.x; ++s) slot0 = slot_before(slot0, s, prefix, sr.n, e.tile_tokens);
     slot0 = min(slot0, e.max_slots - 1);
